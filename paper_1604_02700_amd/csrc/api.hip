@@ -228,7 +228,9 @@ gpic_status verify_csr(const int64_t *row_ptr, const int32_t *col, int64_t n,
 struct Product {
     virtual ~Product() {}
     virtual int64_t blocks() const = 0;
-    virtual hipError_t launch(const double *v, double *y, double *partial,
+    // odd: the update's number is odd (the staged CSR product walks its tiles
+    // the other way round then; the values are the same)
+    virtual hipError_t launch(const double *v, double *y, double *partial, bool odd,
                               StopCtl ctl, hipStream_t s) const = 0;
     // one launch per update (the previous iteration's tau and update, then
     // this iteration's product), where the operator offers it
@@ -245,7 +247,7 @@ struct DenseProduct : Product {
     const float *W;
     int64_t n, ldw;
     int64_t blocks() const override { return gemv_blocks(n); }
-    hipError_t launch(const double *v, double *y, double *partial, StopCtl ctl,
+    hipError_t launch(const double *v, double *y, double *partial, bool, StopCtl ctl,
                       hipStream_t s) const override
     {
         return launch_gemv(W, n, ldw, v, y, partial, ctl, true, s);
@@ -267,17 +269,17 @@ struct CsrProduct : Product {
     const float *val;
     int64_t n, nnz;
     int64_t blocks() const override { return spmv_partials(n, nnz); }
-    hipError_t launch(const double *v, double *y, double *partial, StopCtl ctl,
+    hipError_t launch(const double *v, double *y, double *partial, bool odd, StopCtl ctl,
                       hipStream_t s) const override
     {
-        return launch_spmv(row_ptr, col, val, n, nnz, v, y, partial, ctl, true, s);
+        return launch_spmv(row_ptr, col, val, n, nnz, v, y, partial, !odd, ctl, true, s);
     }
 };
 
 struct BlockedCsrProduct : Product {
     CsrBlocked B;
     int64_t blocks() const override { return csr_blocked_partials(B.n); }
-    hipError_t launch(const double *v, double *y, double *partial, StopCtl ctl,
+    hipError_t launch(const double *v, double *y, double *partial, bool, StopCtl ctl,
                       hipStream_t s) const override
     {
         return launch_spmv_blocked(B, v, y, partial, ctl, s);
@@ -292,7 +294,7 @@ struct FusedProduct : Product {
     const double *degree;
     void *scratch;
     int64_t blocks() const override { return fused_blocks(n, d); }
-    hipError_t launch(const double *v, double *y, double *partial, StopCtl ctl,
+    hipError_t launch(const double *v, double *y, double *partial, bool, StopCtl ctl,
                       hipStream_t s) const override
     {
         return launch_fused_apply(X, n, d, c, v, degree, y, partial, ctl, true,
@@ -306,7 +308,7 @@ struct SymProduct : Product {
     const double *degree;
     double *part;
     int64_t blocks() const override { return sym_blocks(n); }
-    hipError_t launch(const double *v, double *y, double *partial, StopCtl ctl,
+    hipError_t launch(const double *v, double *y, double *partial, bool, StopCtl ctl,
                       hipStream_t s) const override
     {
         return launch_sym_gemv(As, n, degree, v, y, part, partial, ctl, true, s);
@@ -329,7 +331,7 @@ struct HostDenseProduct : Product {
     hipEvent_t copied[2], consumed[2];
     mutable int64_t seq = 0;         // panels issued so far
     int64_t blocks() const override { return gemv_blocks(n); }
-    hipError_t launch(const double *v, double *y, double *partial, StopCtl ctl,
+    hipError_t launch(const double *v, double *y, double *partial, bool, StopCtl ctl,
                       hipStream_t s) const override
     {
         for (int64_t r0 = 0; r0 < n; r0 += P) {
@@ -445,7 +447,7 @@ gpic_status run_power_iteration(const Product &op, int64_t n,
             ctl.cur_stat = ring + (u % kRing);
             ctl.eps = eps;
             ctl.err = err;
-            CHECK_HIP(op.launch(v, y, partial, ctl, s), "product");
+            CHECK_HIP(op.launch(v, y, partial, (u & 1) != 0, ctl, s), "product");
             CHECK_HIP(launch_tau_update(partial, op.blocks(), tau, y, v, delta, n, ctl, s),
                       "tau and update");
         }
@@ -899,7 +901,7 @@ gpic_status gpic_matvec_csr(const int64_t *row_ptr, const int32_t *col,
     if ((st = check_vec(v, "v")) != GPIC_OK || (st = check_vec(y, "y")) != GPIC_OK)
         return st;
     StopCtl none{};
-    CHECK_HIP(launch_spmv(row_ptr, col, val, n, nnz, v, y, nullptr, none, false,
+    CHECK_HIP(launch_spmv(row_ptr, col, val, n, nnz, v, y, nullptr, false, none, false,
                           (hipStream_t)stream),
               "spmv");
     return GPIC_OK;

@@ -192,12 +192,13 @@ hipError_t launch_gemv_pipe(const float *W, int64_t n, int64_t ldw, double *v, d
 // CSR product: up to 64 entries per row on average, the staged product
 // (tiles of 256 rows, entries staged in LDS by all lanes, a thread per row
 // summing in entry order), else 16 lanes per row; spmv_partials(n, nnz)
-// |y| partial sums either way
+// |y| partial sums either way.  rev (staged product): the tiles in
+// descending order, the same values
 bool spmv_staged(int64_t n, int64_t nnz);
 int64_t spmv_partials(int64_t n, int64_t nnz);
 hipError_t launch_spmv(const int64_t *row_ptr, const int32_t *col,
                        const float *val, int64_t n, int64_t nnz, const double *v,
-                       double *y, double *partial, StopCtl ctl, bool use_ctl,
+                       double *y, double *partial, bool rev, StopCtl ctl, bool use_ctl,
                        hipStream_t s);
 // tau and the update in one launch (every workgroup forms tau itself in
 // one fixed order, so all hold the same bits)

@@ -105,12 +105,20 @@ __global__ __launch_bounds__(kThreads) void spmv_kernel(
 // current round's rows are summed.  Tiles are numbered XCD-major: the
 // workgroups one XCD runs hold a contiguous eighth of the rows, so with a
 // numbering that keeps graph neighbours close, the v entries an XCD
-// gathers stay in its L2.
+// gathers stay in its L2.  With rev every XCD walks its tiles from the last
+// to the first: the power iteration alternates the direction, so an update
+// begins with the tiles whose entries and v the one before touched last
+// (L2 and the 256 MB Infinity Cache still hold them); every row's sum and
+// every partial's place are the same.  n = 2M, 90M entries: the loop to
+// convergence 9.62 -> 9.01 ms (the product waits for loads, and these come
+// back sooner).  The dense and symmetric products, which already stream at
+// the rate a plain read reaches, gained nothing from it (n = 10,000 to
+// 50,000) and keep one direction.
 __global__ __launch_bounds__(kThreads) void spmv_staged_kernel(
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
     const float *__restrict__ val, int64_t n, int64_t tiles, int64_t per_xcd,
     const double *__restrict__ v, double *__restrict__ y, double *__restrict__ partial,
-    StopCtl ctl, int use_ctl)
+    int rev, StopCtl ctl, int use_ctl)
 {
     __shared__ int64_t rp[kStagedRows + 1];
     __shared__ double ps[kStage];
@@ -121,7 +129,8 @@ __global__ __launch_bounds__(kThreads) void spmv_staged_kernel(
         if (stop_reached(ctl))
             return;
     }
-    const int64_t tile = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    const int64_t q = blockIdx.x / kXcds;
+    const int64_t tile = (int64_t)(blockIdx.x % kXcds) * per_xcd + (rev ? per_xcd - 1 - q : q);
     if (tile >= tiles)
         return;                                      // uniform over the workgroup
     const int64_t row0 = tile * kStagedRows;
@@ -308,14 +317,14 @@ int64_t spmv_partials(int64_t n, int64_t nnz)
 
 hipError_t launch_spmv(const int64_t *row_ptr, const int32_t *col,
                        const float *val, int64_t n, int64_t nnz, const double *v,
-                       double *y, double *partial, StopCtl ctl, bool use_ctl,
+                       double *y, double *partial, bool rev, StopCtl ctl, bool use_ctl,
                        hipStream_t s)
 {
     if (spmv_staged(n, nnz)) {
         const int64_t tiles = (n + kStagedRows - 1) / kStagedRows;
         const int64_t per = (tiles + kXcds - 1) / kXcds;
         hipLaunchKernelGGL(spmv_staged_kernel, dim3((unsigned)(per * kXcds)), dim3(kThreads),
-                           0, s, row_ptr, col, val, n, tiles, per, v, y, partial, ctl,
+                           0, s, row_ptr, col, val, n, tiles, per, v, y, partial, rev ? 1 : 0, ctl,
                            use_ctl ? 1 : 0);
     } else {
         hipLaunchKernelGGL(spmv_kernel, dim3((unsigned)spmv_blocks(n)),
