@@ -18,6 +18,8 @@
 //   4. backtrack, per-cluster means and sums of squares, labels by
 //      ascending centroid.
 #include "common.h"
+#include "kmeans_dev.h"
+#include "kmeans_windows.h"
 
 namespace gpic {
 namespace {
@@ -224,16 +226,6 @@ __global__ __launch_bounds__(kThreads) void prefix_kernel(
         SS[0] = double2{0.0, 0.0};
 }
 
-// cost(j, i) from the prefix sums at j and i + 1
-__device__ __forceinline__ double seg_cost(double2 a, double2 e, int64_t j, int64_t i)
-{
-    const double m = (double)(i - j + 1);
-    const double s1 = e.x - a.x;
-    const double s2 = e.y - a.y;
-    const double c = s2 - s1 * s1 / m;
-    return c > 0.0 ? c : 0.0;
-}
-
 // A layer's values as its successor reads them: E[j] = D(j - 1) where j
 // starts a run of equal values, +infinity where it does not (a split there
 // would separate equal values), so a candidate needs no separate flag.
@@ -304,16 +296,6 @@ __host__ __device__ __forceinline__ int32_t sample_row(int32_t lo, int32_t hi, i
     return lo + (int32_t)(f1 * a + (f1 * b) / (F + 1)) - 1;
 }
 
-// Leftmost-argmin merge of (value, index) pairs.
-__device__ __forceinline__ void amin_merge(double &b, int64_t &a, double ob,
-                                           int64_t oa)
-{
-    if (ob < b || (ob == b && oa < a)) {
-        b = ob;
-        a = oa;
-    }
-}
-
 // Scan split points j = from .. ahi for row r, keeping the leftmost
 // minimum of D(j - 1) + cost(j, r) over run starts (E[j] is +infinity
 // elsewhere, and so is the sum).  Every candidate is evaluated without
@@ -332,54 +314,6 @@ __device__ __forceinline__ void scan_range(const double2 *__restrict__ SS,
             arg = j;
         }
     }
-}
-
-// The value of lane (lane xor K): data-parallel moves for K = 1, 2, 8
-// (quad permutations, a rotation by 8 within a row of 16), swizzles for
-// K = 4, 16, a permute for K = 32.
-template <int K>
-__device__ __forceinline__ int lane_xor(int x)
-{
-    if (K == 1)
-        return __builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, false);
-    if (K == 2)
-        return __builtin_amdgcn_mov_dpp(x, 0x4e, 0xf, 0xf, false);
-    if (K == 4)
-        return __builtin_amdgcn_ds_swizzle(x, 0x101f);
-    if (K == 8)
-        return __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, false);
-    if (K == 16)
-        return __builtin_amdgcn_ds_swizzle(x, 0x401f);
-    return __shfl_xor(x, 32, kWave);
-}
-
-template <int K>
-__device__ __forceinline__ void argmin_step(double &best, int32_t &arg)
-{
-    const long long bb = __double_as_longlong(best);
-    const int lo = lane_xor<K>((int)(bb & 0xffffffffll));
-    const int hi = lane_xor<K>((int)(bb >> 32));
-    const double ob = __longlong_as_double(((long long)(unsigned)hi << 32) |
-                                           (long long)(unsigned)lo);
-    const int32_t oa = lane_xor<K>(arg);
-    if (ob < best || (ob == best && oa < arg)) {
-        best = ob;
-        arg = oa;
-    }
-}
-
-// Leftmost minimum of (value, index) over the wave, in every lane (an
-// index of INT64_MAX, no candidate, travels as INT32_MAX).
-__device__ __forceinline__ void wave_argmin(double &best, int64_t &arg)
-{
-    int32_t a = (arg == INT64_MAX) ? INT32_MAX : (int32_t)arg;
-    argmin_step<32>(best, a);
-    argmin_step<16>(best, a);
-    argmin_step<8>(best, a);
-    argmin_step<4>(best, a);
-    argmin_step<2>(best, a);
-    argmin_step<1>(best, a);
-    arg = (a == INT32_MAX) ? INT64_MAX : (int64_t)a;
 }
 
 // Candidate bounds of interval [lo, hi]: [alo, ohi]; row r takes j <= r.
@@ -1036,7 +970,14 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     const int64_t distinct = (int64_t)hsc.distinct;
     const int ke = (int)((int64_t)k < distinct ? k : distinct);
 
-    // 3. layers
+    // 3. layers: inside windows around the optimal cuts where these can be
+    // found, else every row; both use the scratch from the split table to
+    // the queue's end, and the sort's spare keys (n float64) and histogram
+    // (a KiB per 4,096 values) are free by now
+    int solved = 0;
+    GPIC_TRY(kmeans_windows(sv, run, SS, n, &sc->mean, ke, (double *)keyB, (double *)hist,
+                            w + L.opt, L.qlen - L.opt, first, s, &solved));
+    if (!solved) {
     hipLaunchKernelGGL(first_layer_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
                        SS, run, n, Ea, Q.qlen);
     const int F = fary_f(n);
@@ -1154,9 +1095,10 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
         }
     }
     GPIC_TRY(hipGetLastError());
-
-    // 4. boundaries, cluster statistics, labels
     hipLaunchKernelGGL(backtrack_kernel, dim3(1), dim3(64), 0, s, opt, n, ke, first);
+    }
+
+    // 4. cluster statistics, labels
     hipLaunchKernelGGL(cluster_stats_kernel, dim3((unsigned)ke), dim3(kStatThreads), 0, s,
                        sv, first, centroids, costs);
     hipLaunchKernelGGL(labels_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s, idxA,

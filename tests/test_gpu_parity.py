@@ -416,6 +416,32 @@ def test_kmeans1d_unclustered(g, orc, n, k):
     check_kmeans(v, out, orc.kmeans1d(v, k, "dc"))
 
 
+@pytest.mark.parametrize("n,k", [(8191, 3), (8192, 3), (8192, 24), (20011, 10), (60000, 24),
+                                 (300007, 12)])
+@pytest.mark.parametrize("shape", ["normal", "tail", "tight", "gaps", "ties", "offset"])
+def test_kmeans1d_windows(g, orc, n, k, shape):
+    """From 8,192 values the layers are solved inside windows around the
+    optimal cuts.  Shapes that stretch the bounds: dense and sparse by turns,
+    clusters 1e-9 wide (values equal to the rounding of the prefix sums),
+    half as many clusters as k, few distinct values, a large offset."""
+    rng = np.random.default_rng(n + 31 * k)
+    if shape == "normal":
+        v = rng.standard_normal(n)
+    elif shape == "tail":
+        v = rng.exponential(1.0, n) ** 3
+    elif shape == "tight":
+        v = rng.random(k)[rng.integers(k, size=n)] + 1e-9 * rng.standard_normal(n)
+    elif shape == "gaps":
+        m = max(2, k // 2)
+        v = rng.random(m)[rng.integers(m, size=n)] + 1e-4 * rng.standard_normal(n)
+    elif shape == "ties":
+        v = np.floor(20.0 * rng.standard_normal(n))
+    else:
+        v = 1e6 + rng.random(n)
+    out = g.gpic_kmeans1d(_t(v), k)
+    check_kmeans(v, out, orc.kmeans1d(v, k, "dc"))
+
+
 def test_kmeans1d_special_values(g, orc):
     v = np.array([3.0, -0.0, 0.0, -2.5, 1e-300, -40.0, 7.0, 3.0])
     for k in (1, 3, 6, 8):
