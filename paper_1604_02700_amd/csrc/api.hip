@@ -631,7 +631,8 @@ gpic_status gpic_affinity_normalized(const float *X, int64_t n, int32_t d,
     CHECK_HIP(launch_start_vector(degree, n, v0, n_zero_rows, ws, s, &bad), "v0");
     if (bad)
         return fail(GPIC_ERR_NUMERIC, "sum of degrees is zero or not finite");
-    CHECK_HIP(launch_affinity_w(X, n, d, c, W, ldw, degree, aws, s), "W sweep");
+    // the degree sweep left the operands of the same points in aws
+    CHECK_HIP(launch_affinity_w(X, n, d, c, W, ldw, degree, aws, s, true), "W sweep");
     return GPIC_OK;
 }
 

@@ -116,7 +116,7 @@ hipError_t launch_affinity(const float *X, int64_t n, int d, float c_log2,
                            hipStream_t s);
 hipError_t launch_affinity_w(const float *X, int64_t n, int d, float c_log2,
                              float *W, int64_t ldw, const double *degree,
-                             void *ws, hipStream_t s);
+                             void *ws, hipStream_t s, bool operands_ready = false);
 hipError_t launch_fused_degree(const float *X, int64_t n, int d, float c_log2,
                                double *degree, void *ws, hipStream_t s);
 // Augmented operands for the matrix-core engine, once for a run of
