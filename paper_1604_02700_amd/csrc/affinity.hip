@@ -48,7 +48,8 @@
 //            rows, and for columns past its
 //            rows A_ij v_i also goes to column sums that a second kernel
 //            adds to the later rows (fused_sym_reduce_kernel).  With v = 1
-//            and no division it is the degree sweep of that same A.
+//            and no division it is the degree sweep of that same A.  Below
+//            16 dimensions affinity_valu_sym_kernel is its difference form.
 // Every mode evaluates the same float32 A_ij for a (row i, column j) pair
 // and sums rows in the same order, so kDegree reproduces kStore's degrees
 // bit for bit and kStoreW writes exactly what kStore followed by the row
@@ -1021,6 +1022,223 @@ __global__ __launch_bounds__(kThreads) void affinity_valu_kernel(
         partial[blockIdx.x] = part;
 }
 
+// The fused product from coordinate differences with each pair evaluated
+// once (d < 16; the value is the same whichever point comes first: the
+// differences are squared).  Bound by vector issue, d subtractions, d
+// multiply-adds, a multiply, exp2 (four issue slots) and a conversion per
+// pair, so a pair evaluated for both of its rows costs about half of two;
+// what is added is one more float64 multiply-add and the column sums.
+// A workgroup's 4 waves own 256 rows and take the columns of their chunk
+// from their own first row on, in tiles of 128 staged through
+// double-buffered LDS, coordinate-major.  Lane (rl, cl) = (lane % 8, lane /
+// 8) holds 8 rows in registers and evaluates them against 4 columns at a
+// time, so a column read from LDS serves 8 pairs; its row sums stay in
+// registers to the end, and for columns past the workgroup's rows the 4
+// column sums are reduce-scattered over the 8 lanes rl, then added over the
+// waves through LDS: one float64 per (256 rows, column) goes to colpart,
+// which fused_sym_reduce_kernel adds to the later rows.
+// us per product, against every ordered pair in affinity_valu_kernel: n =
+// 40,013, d = 2, 5, 8, 15: 296, 414, 524, 964 against 477, 669, 937, 1,973;
+// n = 100,000, d = 5: 2,243 against 3,984 (2.2e12 pairs/s, 17.6 issue slots
+// a pair).
+constexpr int kVsRows = 256;
+constexpr int kVsCols = 128;
+constexpr int kVsLaneRows = 8;
+// rows of a lane evaluated together (4 need spills above 8 coordinates)
+constexpr int vs_step(int d) { return d <= 8 ? 4 : 2; }
+
+// The float64 of lane (lane xor K), K = 1, 2 (data-parallel moves) or 4 (a
+// swizzle), on the two halves of the value.
+template <int K>
+__device__ __forceinline__ double xor_lane(double x)
+{
+    const long long b = __double_as_longlong(x);
+    int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
+    if (K == 4) {
+        lo = __builtin_amdgcn_ds_swizzle(lo, 0x101f);
+        hi = __builtin_amdgcn_ds_swizzle(hi, 0x101f);
+    } else {
+        constexpr int ctrl = (K == 1) ? 0xb1 : 0x4e;
+        lo = __builtin_amdgcn_mov_dpp(lo, ctrl, 0xf, 0xf, false);
+        hi = __builtin_amdgcn_mov_dpp(hi, ctrl, 0xf, 0xf, false);
+    }
+    return __longlong_as_double(((long long)(unsigned)hi << 32) | (long long)(unsigned)lo);
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void affinity_valu_sym_kernel(
+    const float *__restrict__ X, int64_t n, float c, int64_t chunk_cols,
+    const double *__restrict__ v, double *__restrict__ part, double *__restrict__ colpart,
+    StopCtl ctl, int use_ctl)
+{
+    constexpr int kW = kThreads / kWave;
+    constexpr int RB = kVsLaneRows;
+    constexpr int kStep = vs_step(D);
+    static_assert(kW * 8 * RB == kVsRows, "rows of a workgroup");
+    __shared__ float xs[2][D][kVsCols];
+    __shared__ double vs[2][kVsCols];
+    __shared__ double cred[2][kW][kVsCols];
+    if (use_ctl) {
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+            *ctl.cur_stat = 0.0;
+        if (stop_reached(ctl))
+            return;
+    }
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int rl = lane & 7, cl = lane >> 3;
+    const int64_t grow0 = (int64_t)blockIdx.x * kVsRows, grow1 = grow0 + kVsRows;
+    int64_t c0 = (int64_t)blockIdx.y * chunk_cols;
+    const int64_t c1 = (c0 + chunk_cols < n) ? c0 + chunk_cols : n;
+    if (grow0 > c0)
+        c0 = grow0;
+    if (c0 >= c1)
+        return;                                      // uniform over the workgroup
+    const int64_t row0 = grow0 + (wave * 8 + rl) * RB;   // this lane's 8 rows
+    float xi[RB][D];
+    double vi[RB], acc[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        const int64_t i = row0 + r, ic = i < n ? i : n - 1;
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            xi[r][k] = X[ic * D + k];
+        vi[r] = (i < n) ? (v != nullptr ? v[i] : 1.0) : 0.0;
+        acc[r] = 0.0;
+    }
+    // a tile's coordinates are kVsCols D consecutive floats (zeros past n, not
+    // a point that may be infinite), each thread taking every kThreads-th
+    constexpr int kPer = (kVsCols * D + kThreads - 1) / kThreads;
+    float st[kPer];
+    double vst = 0.0;
+    const int64_t last = n * D - 1;
+    auto fetch = [&](int64_t jt) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int64_t e = jt * D + threadIdx.x + u * kThreads;
+            st[u] = (e <= last) ? X[e] : 0.0f;
+        }
+        if (threadIdx.x < kVsCols) {
+            const int64_t j = jt + threadIdx.x;
+            vst = (j < c1) ? (v != nullptr ? v[j] : 1.0) : 0.0;
+        }
+    };
+    auto commit = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int f = threadIdx.x + u * kThreads;
+            if (f < kVsCols * D)
+                xs[buf][f % D][f / D] = st[u];
+        }
+        if (threadIdx.x < kVsCols)
+            vs[buf][threadIdx.x] = vst;
+    };
+    // Columns past n (zeros, with v = 0) add nothing to a row and leave no
+    // column sum, so only the diagonal needs a mask.
+    auto tile = [&](int buf, int64_t jt, auto offdiag) {
+        constexpr bool kOff = decltype(offdiag)::value;
+        const int rowc = kOff ? 0 : (int)(row0 - jt);    // this lane's first row as a column
+#pragma unroll 1
+        for (int q0 = 0; q0 < kVsCols; q0 += 32) {
+            const int cb = q0 + 4 * cl;              // this lane's 4 columns
+            double vj[4], cs[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                vj[q] = vs[buf][cb + q];
+                cs[q] = 0.0;
+            }
+#pragma unroll
+            for (int r0 = 0; r0 < RB; r0 += kStep) {
+                float s[kStep][4];
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    const floatx4 xj = *reinterpret_cast<const floatx4 *>(&xs[buf][k][cb]);
+#pragma unroll
+                    for (int r = 0; r < kStep; ++r)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float df = xi[r0 + r][k] - xj[q];
+                            s[r][q] = (k == 0) ? df * df : fmaf(df, df, s[r][q]);
+                        }
+                }
+#pragma unroll
+                for (int r = 0; r < kStep; ++r)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float a = exp2_fast(-c * s[r][q]);
+                        if (!kOff && rowc + r0 + r == cb + q)
+                            a = 0.0f;
+                        const double a64 = (double)a;
+                        acc[r0 + r] = fma(a64, vj[q], acc[r0 + r]);
+                        if (kOff)
+                            cs[q] = fma(a64, vi[r0 + r], cs[q]);
+                    }
+                __builtin_amdgcn_sched_barrier(0);   // one group of rows' registers at a time
+            }
+            if (kOff) {
+                // after xor 1 and xor 2 lane rl holds column 2 (rl & 1) +
+                // (rl >> 1 & 1) over four lanes' rows, xor 4 adds the other four
+                const bool b0 = (rl & 1) != 0, b1 = (rl & 2) != 0;
+                double h[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const double send = b0 ? cs[q] : cs[q + 2];
+                    const double keep = b0 ? cs[q + 2] : cs[q];
+                    h[q] = keep + xor_lane<1>(send);
+                }
+                const double send = b1 ? h[0] : h[1];
+                const double keep = b1 ? h[1] : h[0];
+                double t = keep + xor_lane<2>(send);
+                t = t + xor_lane<4>(t);
+                if (rl < 4)
+                    cred[buf][wave][cb + 2 * (rl & 1) + (rl >> 1)] = t;
+            }
+        }
+    };
+    const int64_t ntiles = (c1 - c0 + kVsCols - 1) / kVsCols;
+    fetch(c0);
+    commit(0);
+    __syncthreads();
+    for (int64_t t = 0; t < ntiles; ++t) {
+        const int buf = (int)(t & 1);
+        const int64_t jt = c0 + t * kVsCols;
+        if (t + 1 < ntiles)
+            fetch(jt + kVsCols);                     // in flight during compute
+        const bool off = jt >= grow1;
+        if (off)
+            tile(buf, jt, std::true_type{});
+        else
+            tile(buf, jt, std::false_type{});
+        // the barrier ending the previous iteration ordered every wave's reads
+        // of buffer buf ^ 1 before these writes
+        if (t + 1 < ntiles)
+            commit(buf ^ 1);
+        __syncthreads();
+        if (off && threadIdx.x < kVsCols) {
+            // the tile's column sums in wave order (cred[buf] is written again
+            // two tiles on, behind the next barrier)
+            const int64_t j = jt + threadIdx.x;
+            if (j < c1) {
+                double t2 = 0.0;
+#pragma unroll
+                for (int w = 0; w < kW; ++w)
+                    t2 += cred[buf][w][threadIdx.x];
+                colpart[colpart_offset(blockIdx.x, n, kVsRows) + (j - grow1)] = t2;
+            }
+        }
+    }
+    // the 8 lanes cl sharing a row hold disjoint columns
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        double t = acc[r];
+        t += __shfl_xor(t, 8, kWave);
+        t += __shfl_xor(t, 16, kWave);
+        t += __shfl_xor(t, 32, kWave);
+        const int64_t i = row0 + r;
+        if (cl == 0 && i < n)
+            part[(int64_t)blockIdx.y * n + i] = t;
+    }
+}
+
 // ------------------------------------------------------------- dispatch
 
 bool use_mfma(int d) { return d >= 16 && d <= 128; }
@@ -1088,7 +1306,17 @@ int64_t padded_points(int64_t n) { return (n + kColAlign - 1) / kColAlign * kCol
 // the product sums whole rows.
 constexpr int64_t kFusedSymMaxN = 1 << 19;
 
-bool fused_sym(int64_t n, int d) { return use_mfma(d) && n <= kFusedSymMaxN; }
+// Below 16 dimensions from 10,000 points on: with fewer the (256 rows, chunk)
+// pieces leave much of the chip idle (per product at n = 8,000, d = 2, 5, 8:
+// 32, 42, 52 us against 28, 38, 51 with every ordered pair; at 20,000: 100,
+// 140, 176 against 130, 181, 252).
+constexpr int64_t kValuSymMinN = 10000;
+
+bool valu_sym(int64_t n, int d) { return d < 16 && n >= kValuSymMinN && n <= kFusedSymMaxN; }
+bool fused_sym(int64_t n, int d)
+{
+    return (use_mfma(d) && n <= kFusedSymMaxN) || valu_sym(n, d);
+}
 
 // Column partial sums of the symmetric product for row groups of G rows:
 // the smaller G (256 rows, above 64 coordinates) needs the most entries,
@@ -1368,7 +1596,7 @@ hipError_t launch_fused_apply(const float *X, int64_t n, int d, float c,
         return dispatch<kApply>(X, n, d, c, nullptr, 0, v, degree, y, partial, ctl,
                                 use_ctl ? 1 : 0, ws, s, operands_ready);
     const Ws w = carve(ws, n);
-    if (!operands_ready) {
+    if (use_mfma(d) && !operands_ready) {
         const hipError_t e = launch_split(X, n, d, c, w, s);
         if (e != hipSuccess)
             return e;
@@ -1378,6 +1606,22 @@ hipError_t launch_fused_apply(const float *X, int64_t n, int d, float c,
     int nchunks;
     sym_chunking(n, &chunk_cols, &nchunks);
     const int uc = use_ctl ? 1 : 0;
+    int64_t G = kVsRows;
+    if (!use_mfma(d)) {
+        const dim3 grid((unsigned)((n + kVsRows - 1) / kVsRows), (unsigned)nchunks);
+#define GPIC_VALU(D)                                                                        \
+    case D:                                                                                 \
+        hipLaunchKernelGGL(affinity_valu_sym_kernel<D>, grid, dim3(kThreads), 0, s, X, n, c, \
+                           chunk_cols, v, w.part, colpart, ctl, uc);                        \
+        break;
+        switch (d) {
+            GPIC_VALU(1) GPIC_VALU(2) GPIC_VALU(3) GPIC_VALU(4) GPIC_VALU(5)
+            GPIC_VALU(6) GPIC_VALU(7) GPIC_VALU(8) GPIC_VALU(9) GPIC_VALU(10)
+            GPIC_VALU(11) GPIC_VALU(12) GPIC_VALU(13) GPIC_VALU(14) GPIC_VALU(15)
+        default: return hipErrorInvalidValue;        // not reached: valu_sym
+        }
+#undef GPIC_VALU
+    } else {
 #define GPIC_MFMA(NCH)                                                                \
     launch_engine<NCH, kApplySym>(w, n, chunk_cols, nchunks, nullptr, 0, v, degree,   \
                                   nullptr, w.part, nullptr, ctl, uc, s, colpart)
@@ -1388,7 +1632,8 @@ hipError_t launch_fused_apply(const float *X, int64_t n, int d, float c,
     default: GPIC_MFMA(4); break;
     }
 #undef GPIC_MFMA
-    const int64_t G = rows_per_group(kApplySym, nch_for(d));
+    G = rows_per_group(kApplySym, nch_for(d));
+    }
     hipLaunchKernelGGL(fused_sym_reduce_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, s, w.part, nchunks, chunk_cols, colpart, n, G, degree,
                        y, partial, ctl, uc);

@@ -493,6 +493,42 @@ def test_fused_symmetric_edges(g, orc, n, d):
     np.testing.assert_allclose(y, yr, rtol=1e-5)
 
 
+@pytest.mark.parametrize("n,d", [(9999, 3), (10000, 1), (10240, 2), (10241, 8), (10113, 9),
+                                 (12037, 5), (10495, 15)])
+def test_fused_symmetric_few_dimensions(g, orc, n, d):
+    """Below 16 dimensions the fused operator evaluates each pair once from
+    10,000 points on (256-row groups, 128-column tiles, coordinates in steps
+    of 4 rows up to 8 dimensions, 2 above): sizes around the switch and the
+    group and tile edges, degrees and a product against the oracle's rows
+    (relative bound of the float32 distances), W 1 = 1 to float64 rounding."""
+    X = _pts(n, d, 90 + d, scale=1.2)
+    sigma = np.float32(np.sqrt(d))
+    deg, _, _ = g.gpic_degree_fused(_t(X), sigma)
+    dr, _, _ = orc.degree_onthefly(X, sigma)
+    np.testing.assert_allclose(deg.cpu().numpy(), dr, rtol=1e-5)
+    v = np.random.default_rng(n + d).uniform(0.5, 1.5, size=n)
+    y = g.gpic_matvec_fused(_t(X), sigma, deg, _t(v)).cpu().numpy()
+    rows = np.unique(np.r_[0:300, n // 2 - 3:n // 2 + 300, n - 300:n]).astype(np.int64)
+    yr = orc.matvec_onthefly_rows(X, sigma, dr, v, rows)
+    np.testing.assert_allclose(y[rows], yr, rtol=1e-5)
+    ones = torch.ones(n, dtype=torch.float64, device=DEV)
+    y1 = g.gpic_matvec_fused(_t(X), sigma, deg, ones).cpu().numpy()
+    np.testing.assert_allclose(y1, 1.0, rtol=1e-12)
+
+
+def test_fused_few_dimensions_far_point(g):
+    """An infinite coordinate in the last point (whose tile is padded): its
+    own degree is 0 and no other row notices."""
+    n, d = 10001, 3
+    X = _pts(n, d, 5)
+    X[-1, 0] = np.inf
+    deg, _, nz = g.gpic_degree_fused(_t(X), np.float32(1.5))
+    A, degd = g.gpic_affinity(_t(X), np.float32(1.5))
+    deg, degd = deg.cpu().numpy(), degd.cpu().numpy()
+    assert deg[-1] == 0.0 and int(nz.item()) == 1
+    np.testing.assert_allclose(deg, degd, rtol=1e-12)
+
+
 def test_fused_full_rows_above_symmetric_limit(g, orc):
     """Above 2^19 points the fused operator sums every ordered pair (row
     sweep for the degrees, row products): n = 2^19 + 1, sampled rows
