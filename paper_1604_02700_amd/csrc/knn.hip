@@ -8,10 +8,10 @@
 //
 // Brute force in four steps, exact in the end:
 //   1. bound: the points are put in Morton order of their quantised centred
-//      coordinates; for every row, the k-th smallest float32 squared
-//      distance to the points within 256 positions of it in that order and
-//      to a fixed sample of 65,536 positions, which bounds the true k-th
-//      neighbour distance from above;
+//      coordinates and cut into tiles of 64 consecutive ones; for every row,
+//      the k-th smallest float32 squared distance to the points of the 32
+//      tiles whose boxes are centred nearest to its own tile's, which bounds
+//      the true k-th neighbour distance from above;
 //   2. collect: squared distances on the fp32 matrix cores (Gram form over
 //      the centred points augmented as [x_j, |x_j|^2, 1] .
 //      [-2 x_i, 1, |x_i|^2]), appending every j that passes the row's bound
@@ -20,7 +20,8 @@
 //      spatially compact; a pair of tiles whose bounding boxes are farther
 //      apart than every bound of the row tile is skipped whole (no pair in
 //      it can be a neighbour: its true distance exceeds the row's bound,
-//      which is at least the true k-th neighbour distance);
+//      which is at least the true k-th neighbour distance), and so is each
+//      block of 16 rows by 16 columns of the tiles that remain;
 //   3. select: a wave per row recomputes the candidates' squared distances
 //      in float64 and keeps the k smallest (ties to the smaller index); a
 //      row whose list overflowed gets the k-th distance among the kept
@@ -30,6 +31,7 @@
 //      from float64 distances.
 // Supports d <= 16 and k <= 64.
 #include "common.h"
+#include "kmeans_dev.h"
 
 namespace gpic {
 namespace {
@@ -64,32 +66,72 @@ __device__ __forceinline__ double sq_dist64(const float *__restrict__ X, int d, 
 
 // ------------------------------------------------------------ 1. bound
 
-// Thread per Morton position p, row i = perm[p]: the KT smallest float32
-// squared distances from x_i to the points at positions p - kWindow ..
-// p + kWindow and at the sample positions outside that window (every
-// n / kSample-th position, all of them when n is smaller; each point is
-// counted once), then tau_i = the k-th of them.  The k-th distance to any k
-// other points bounds the true k-th neighbour distance from above: Morton
-// neighbours are mostly near (a tight bound), the sample caps the bound
-// where the Morton order jumps.  Both sets go through LDS 256 points at a
-// time.
-constexpr int kWindow = 256;           // Morton positions on each side
-constexpr int64_t kSample = 65536;     // sample positions
+// The kNear tiles whose box centres lie nearest to a row tile's, nearest
+// first (a workgroup per row tile): each thread keeps the nearest of every
+// 256th tile -- neighbours in Morton order go to different threads -- and
+// the 256 kept are ranked against each other.  With at most 256 tiles
+// these are the nearest of all; else near enough (any tiles give a bound).
+constexpr int kNear = 32;
+constexpr int kWindow = 4;             // tiles on each side in Morton order
 
-__device__ __forceinline__ int64_t sample_point(int64_t t, int64_t n, int64_t m)
+__global__ __launch_bounds__(kThreads) void near_tiles_kernel(const float *__restrict__ box,
+                                                              int64_t nt, int d,
+                                                              int32_t *__restrict__ near)
 {
-    return (m == n) ? t : (t * n) / m;
+    __shared__ uint64_t key[kThreads];
+    const int64_t row = blockIdx.x;
+    float cr[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+        cr[c] = (c < d) ? 0.5f * box[c * nt + row] + 0.5f * box[(16 + c) * nt + row] : 0.0f;
+    uint64_t best = ~0ull;
+    for (int64_t t = threadIdx.x; t < nt; t += kThreads) {
+        float s = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            if (c < d) {
+                const float g = 0.5f * box[c * nt + t] + 0.5f * box[(16 + c) * nt + t] - cr[c];
+                s = fmaf(g, g, s);
+            }
+        // an overflowed or undefined distance ranks last
+        s = (s < INFINITY) ? s : INFINITY;
+        const uint64_t k = ((uint64_t)__float_as_uint(s) << 32) | (uint64_t)(uint32_t)t;
+        best = (k < best) ? k : best;
+    }
+    key[threadIdx.x] = best;
+    __syncthreads();
+    int rank = 0;
+    for (int u = 0; u < kThreads; ++u)
+        rank += (key[u] < best) ? 1 : 0;
+    // threads without a tile rank after every other, so the first
+    // min(kNear, nt) places are filled
+    if (best != ~0ull && rank < kNear)
+        near[row * kNear + rank] = (int32_t)(best & 0xffffffffull);
 }
 
+// A wave per row tile, a thread per Morton position p, row i = perm[p]: the
+// KT smallest float32 squared distances from x_i to the other points of the
+// tile's near tiles and of its neighbours in Morton order, then tau_i = the
+// k-th of them.  The k-th distance to any k other points bounds the true
+// k-th neighbour distance from above, and these tiles hold at least k others
+// (all points when there are no more than kNear tiles).  The Morton
+// neighbours matter where a tile straddles a jump of the order: its box
+// centre then lies far from all of its rows.  Bound by the insertions into the KT kept values, which
+// a wave takes when any of its rows does: the nearer tiles first, and few
+// of them.  (The k-th distance to 512 Morton neighbours and a sample of
+// 65,536 points took 62 ms at n = 2M, k = 32, for a looser bound, 165
+// candidates a row; these tiles 7 ms and 70 candidates.)
 template <int D, int KT>
 __global__ __launch_bounds__(kThreads) void knn_bound_kernel(
-    const float *__restrict__ X, const int32_t *__restrict__ perm, int64_t n, int k,
-    float *__restrict__ tau)
+    const float *__restrict__ X, const int32_t *__restrict__ perm, int64_t n, int64_t nt, int k,
+    const int32_t *__restrict__ near, float *__restrict__ tau)
 {
-    __shared__ float tile[kThreads * D];
-    __shared__ int64_t tid_[kThreads];
-    const int64_t p0 = (int64_t)blockIdx.x * kThreads;
-    const int64_t p = p0 + threadIdx.x;
+    __shared__ float tile[kThreads / kWave][kWave * D];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int64_t row = (int64_t)blockIdx.x * (kThreads / kWave) + wave;
+    if (row >= nt)
+        return;                                  // uniform per wave, no barrier below
+    const int64_t p = row * kTileCols + lane;
     const int64_t pc = p < n ? p : n - 1;
     const int64_t i = perm[pc];
     float xi[D];
@@ -100,58 +142,46 @@ __global__ __launch_bounds__(kThreads) void knn_bound_kernel(
 #pragma unroll
     for (int u = 0; u < KT; ++u)
         best[u] = INFINITY;
-    auto consider = [&](const float *xj) {
-        float s = 0.0f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-            const float df = xi[c] - xj[c];
-            s = fmaf(df, df, s);
-        }
-        if (s < best[KT - 1]) {
-#pragma unroll
-            for (int u = KT - 1; u > 0; --u) {
-                const float lo = best[u - 1];
-                best[u] = (s < lo) ? lo : fminf(s, best[u]);
-            }
-            best[0] = fminf(s, best[0]);
-        }
-    };
-    // the Morton window (positions, skipping p and anything beyond kWindow)
-    for (int64_t q0 = p0 - kWindow; q0 < p0 + kThreads + kWindow; q0 += kThreads) {
-        __syncthreads();
-        const int64_t q = q0 + threadIdx.x;
-        const bool ok = q >= 0 && q < n;
-        const int64_t pt = ok ? (int64_t)perm[q] : 0;
+    const int m = nt < kNear ? (int)nt : kNear;
+    float *own = tile[wave];
+    for (int a = -2 * kWindow - 1; a < m; ++a) {
+        // the tiles within kWindow in Morton order, its own first, then the
+        // near tiles that are not among them
+        const int o = 2 * kWindow + 1 + a;       // 0, 1, 2, .. -> row, row - 1, row + 1, ..
+        const int64_t t = (a < 0) ? row + ((o & 1) ? -(o + 1) / 2 : o / 2)
+                                  : (int64_t)near[row * kNear + a];
+        if (t < 0 || t >= nt || (a >= 0 && t >= row - kWindow && t <= row + kWindow))
+            continue;                            // uniform per wave
+        const int64_t q0 = t * kTileCols;
+        const int cnt = (n - q0 < kTileCols) ? (int)(n - q0) : kTileCols;
+        const int64_t pt = perm[q0 + lane < n ? q0 + lane : n - 1];
+        float xj[D];
 #pragma unroll
         for (int c = 0; c < D; ++c)
-            tile[threadIdx.x * D + c] = ok ? X[pt * D + c] : 0.0f;
-        __syncthreads();
-        for (int u = 0; u < kThreads; ++u) {
-            const int64_t qq = q0 + u;
-            if (qq < 0 || qq >= n || qq == pc || qq < pc - kWindow || qq > pc + kWindow)
-                continue;
-            consider(tile + u * D);
-        }
-    }
-    // the sample positions outside the window (the window already holds
-    // the others, and the row itself)
-    const int64_t m = n < kSample ? n : kSample;
-    for (int64_t t0 = 0; t0 < m; t0 += kThreads) {
-        __syncthreads();
-        const int64_t t = t0 + threadIdx.x;
-        const int64_t q = (t < m) ? sample_point(t, n, m) : -1;
-        tid_[threadIdx.x] = q;
-        const int64_t pt = (q >= 0) ? (int64_t)perm[q] : 0;
+            xj[c] = X[pt * D + c];
+        __builtin_amdgcn_wave_barrier();         // the wave's reads of the tile before
 #pragma unroll
         for (int c = 0; c < D; ++c)
-            tile[threadIdx.x * D + c] = (q >= 0) ? X[pt * D + c] : 0.0f;
-        __syncthreads();
-        const int cnt = (m - t0 < kThreads) ? (int)(m - t0) : kThreads;
+            own[lane * D + c] = xj[c];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         for (int u = 0; u < cnt; ++u) {
-            const int64_t qq = tid_[u];
-            if (qq >= pc - kWindow && qq <= pc + kWindow)
-                continue;
-            consider(tile + u * D);
+            float s = 0.0f;
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const float df = xi[c] - own[u * D + c];
+                s = fmaf(df, df, s);
+            }
+            if (q0 + u == pc)
+                s = INFINITY;                    // not the row itself
+            if (s < best[KT - 1]) {
+#pragma unroll
+                for (int w = KT - 1; w > 0; --w) {
+                    const float lo = best[w - 1];
+                    best[w] = (s < lo) ? lo : fminf(s, best[w]);
+                }
+                best[0] = fminf(s, best[0]);
+            }
         }
     }
     if (p < n) {
@@ -161,6 +191,124 @@ __global__ __launch_bounds__(kThreads) void knn_bound_kernel(
             if (u == k - 1)
                 t = best[u];
         tau[i] = t;
+    }
+}
+
+// The bound again for single rows, from the tiles nearest to the row itself:
+// four workgroups per row tile take, one after another, the rows whose
+// bound is more than kWide times the tile's smallest (flags null: before the
+// first collection; the rows beyond a jump of the Morton order, mostly), or
+// the flagged ones (their lists overflowed).  Nearest tiles by the distance
+// from the point to the box centres as in near_tiles_kernel, then the k-th
+// smallest of the distances to their 2,048 points by bisection on the bit
+// patterns.  A wide bound costs its whole row tile a visit to most of a
+// cluster: n = 2M, d = 8, k = 32, ms per graph here and in the collection
+// with kWide = 4: 11 and 60, 6: 6 and 64, and (one workgroup per row tile)
+// 3: 39 and 57, 12: 18 and 75, without the pass before the first
+// collection: 12 and 85.
+constexpr float kWide = 6.0f;
+constexpr unsigned kRefineParts = 4;   // workgroups per row tile, each every 4th row
+
+__global__ __launch_bounds__(kThreads) void refine_bound_kernel(
+    const float *__restrict__ X, const int32_t *__restrict__ perm, const float *__restrict__ box,
+    int64_t n, int64_t nt, int d, int k, const int *__restrict__ flags, float *__restrict__ tau)
+{
+    constexpr int kW = kThreads / kWave;
+    constexpr int kPts = kNear * kTileCols / kThreads;
+    __shared__ uint64_t key[kThreads];
+    __shared__ int32_t nb[kNear];
+    __shared__ unsigned long long todo;
+    __shared__ int cnt[2][kW];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int64_t p0 = (int64_t)(blockIdx.x / kRefineParts) * kTileCols;
+    if (wave == 0) {
+        const int64_t p = p0 + lane;
+        const int64_t i = p < n ? (int64_t)perm[p] : -1;
+        const float t = (i >= 0) ? tau[i] : INFINITY;
+        float lo = t;
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1)
+            lo = fminf(lo, __shfl_xor(lo, o, kWave));
+        const bool want = i >= 0 && (flags != nullptr ? flags[i] != 0 : t > kWide * lo);
+        const unsigned long long m = __ballot(want && lane % kRefineParts == blockIdx.x % kRefineParts);
+        if (lane == 0)
+            todo = m;
+    }
+    __syncthreads();
+    unsigned long long rows = todo;
+    while (rows != 0) {                          // uniform over the workgroup
+        const int r = __ffsll((long long)rows) - 1;
+        rows &= rows - 1;
+        const int64_t pc = p0 + r;
+        const int64_t i = perm[pc];
+        float xi[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            xi[c] = (c < d) ? X[i * d + c] : 0.0f;
+        uint64_t best = ~0ull;
+        for (int64_t t = threadIdx.x; t < nt; t += kThreads) {
+            float s = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+                if (c < d) {
+                    const float g = 0.5f * box[c * nt + t] + 0.5f * box[(16 + c) * nt + t] - xi[c];
+                    s = fmaf(g, g, s);
+                }
+            s = (s < INFINITY) ? s : INFINITY;
+            const uint64_t kk = ((uint64_t)__float_as_uint(s) << 32) | (uint64_t)(uint32_t)t;
+            best = (kk < best) ? kk : best;
+        }
+        key[threadIdx.x] = best;
+        if (threadIdx.x < kNear)
+            nb[threadIdx.x] = -1;
+        __syncthreads();
+        int rank = 0;
+        for (int u = 0; u < kThreads; ++u)
+            rank += (key[u] < best) ? 1 : 0;
+        if (best != ~0ull && rank < kNear)
+            nb[rank] = (int32_t)(best & 0xffffffffull);
+        __syncthreads();
+        // distances as bit patterns (non-negative floats compare as integers);
+        // padding, the row itself and undefined ones last
+        uint32_t v[kPts];
+#pragma unroll
+        for (int u = 0; u < kPts; ++u) {
+            const int32_t t = nb[u * kW + wave];
+            const int64_t q = (int64_t)t * kTileCols + lane;
+            v[u] = 0x7f800000u;
+            if (t >= 0 && q < n && q != pc) {
+                const int64_t j = perm[q];
+                float s = 0.0f;
+                for (int c = 0; c < d; ++c) {
+                    const float df = X[i * d + c] - X[j * d + c];
+                    s = fmaf(df, df, s);
+                }
+                v[u] = (s < INFINITY) ? __float_as_uint(s) : 0x7f800000u;
+            }
+        }
+        // smallest pattern with at least k values at or below it
+        uint32_t a = 0, b = 0x7f800000u;
+        for (int it = 0; a < b; ++it) {          // at most 31 steps
+            const uint32_t m = a + (b - a) / 2;
+            int c = 0;
+#pragma unroll
+            for (int u = 0; u < kPts; ++u)
+                c += __popcll(__ballot(v[u] <= m));
+            if (lane == 0)
+                cnt[it & 1][wave] = c;
+            __syncthreads();
+            c = 0;
+#pragma unroll
+            for (int w = 0; w < kW; ++w)
+                c += cnt[it & 1][w];
+            if (c >= k)
+                b = m;
+            else
+                a = m + 1;
+        }
+        if (threadIdx.x == 0)
+            tau[i] = fminf(tau[i], __uint_as_float(a));
+        __syncthreads();                         // key and nb are refilled for the next row
     }
 }
 
@@ -201,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void threshold_kernel(
         return;
     }
     const double eps = (double)kEps32;
-    const double base = (kth != nullptr) ? kth[i] : (double)tau[i];
+    const double base = (kth != nullptr) ? fmin(kth[i], (double)tau[i]) : (double)tau[i];
     const double t = base * (1.0 + 4.0 * (d + 2) * eps) +
                      (2 * kp + 20) * eps * ((double)norm2[i] + (double)__uint_as_float(*maxn));
     float f = (float)t;
@@ -316,12 +464,18 @@ __global__ __launch_bounds__(kThreads) void morton_key_kernel(
     idx[p] = (int32_t)p;
 }
 
-// Bounding box of the raw coordinates of every tile of kTileCols
-// consecutive positions: box[t][c] = min, box[t][16 + c] = max.  A thread
-// per (tile, coordinate); padding positions are left out.
+// Bounding boxes of the raw coordinates of every block of 16 consecutive
+// positions and of every tile of 64, coordinate-major so that neighbouring
+// tiles' boxes are read together: the lowest values at [c nb + b], the
+// highest at [(16 + c) nb + b] for the nb blocks (tiles).  A thread per
+// (tile, coordinate); padding positions are left out (a block of them is
+// empty: lowest +infinity, highest -infinity, never near anything).
+constexpr int kBlock = 16;
+constexpr int kBlocks = kTileCols / kBlock;
+
 __global__ __launch_bounds__(kThreads) void tile_box_kernel(
     const float *__restrict__ X, const int32_t *__restrict__ perm, int64_t n, int d,
-    int64_t ntiles, float *__restrict__ box)
+    int64_t ntiles, float *__restrict__ box, float *__restrict__ sub)
 {
     const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (e >= ntiles * 16)
@@ -330,14 +484,33 @@ __global__ __launch_bounds__(kThreads) void tile_box_kernel(
     const int c = (int)(e % 16);
     if (c >= d)
         return;
+    const int64_t nb = ntiles * kBlocks;
     float lo = INFINITY, hi = -INFINITY;
-    for (int64_t p = t * kTileCols; p < (t + 1) * kTileCols && p < n; ++p) {
-        const float x = X[(int64_t)perm[p] * d + c];
-        lo = fminf(lo, x);
-        hi = fmaxf(hi, x);
+    for (int b = 0; b < kBlocks; ++b) {
+        float l = INFINITY, h = -INFINITY;
+        for (int64_t p = t * kTileCols + b * kBlock; p < t * kTileCols + (b + 1) * kBlock && p < n;
+             ++p) {
+            const float x = X[(int64_t)perm[p] * d + c];
+            l = fminf(l, x);
+            h = fmaxf(h, x);
+        }
+        sub[c * nb + t * kBlocks + b] = l;
+        sub[(16 + c) * nb + t * kBlocks + b] = h;
+        lo = fminf(lo, l);
+        hi = fmaxf(hi, h);
     }
-    box[t * 32 + c] = lo;
-    box[t * 32 + 16 + c] = hi;
+    box[c * ntiles + t] = lo;
+    box[(16 + c) * ntiles + t] = hi;
+}
+
+// Whether two boxes are farther apart than any of the bounds (the largest
+// being `cut`): the float32 squared gap is within 2e-6 of the exact one
+// relatively (differences, squares and d <= 16 additions, each rounded
+// once), so a gap above cut (1 + 8e-6) is truly above cut.
+__device__ __forceinline__ float box_gap2(float lo, float hi, float rlo, float rhi, float s)
+{
+    const float g = fmaxf(fmaxf(lo - rhi, rlo - hi), 0.0f);
+    return fmaf(g, g, s);
 }
 
 // 4 waves x 16 rows; all columns in tiles of 64 through double-buffered
@@ -345,22 +518,31 @@ __global__ __launch_bounds__(kThreads) void tile_box_kernel(
 // v_mfma_f32_16x16x4f32 with the A operand on the columns and the B operand
 // on the wave's rows, so lane (m, g) holds row wrow0 + m and columns
 // 16 q + 4 g + r of block q.  Every (i, j != i) whose squared distance
-// passes thr_i is appended to row i's list (an integer atomic counter;
-// slots beyond kCap are counted, not written).
+// passes thr_i is appended to row i's list (slots beyond kCap are counted,
+// not written).  A row belongs to one workgroup, so its counter is in LDS
+// until the end.  Bound by the matrix cores and the comparison of their
+// results (1,260 tiles of 64 visited per row tile at n = 2M, d = 8, k = 32
+// before the blocks' boxes, which leave 0.57 of the pairs).  Per graph there:
+// 101 ms; 92 with the counters in LDS; 64 with tighter bounds, coordinate-
+// major boxes and the blocks.
 template <int KS>
 __global__ __launch_bounds__(kThreads) void knn_collect_kernel(
     const float *__restrict__ xa, int64_t np, const float *__restrict__ xb, int64_t n, int d,
     const int32_t *__restrict__ perm, const float *__restrict__ box,
-    const float *__restrict__ thr, int *__restrict__ count, int32_t *__restrict__ cand)
+    const float *__restrict__ sub, const float *__restrict__ thr, int *__restrict__ count,
+    int32_t *__restrict__ cand)
 {
     constexpr int KP = 4 * KS;
     constexpr int kRow4 = kTileCols / 4;
     static_assert(kRowsPerGroup == kTileCols, "a row group is one tile");
     __shared__ floatx4 xs[2][KP * kRow4];
     __shared__ int tl[kThreads];                 // column tiles of the current chunk
+    __shared__ unsigned short tm[kThreads];      // their blocks: bit 4 wave + q
     __shared__ int wcnt[kThreads / kWave];
     __shared__ float wmax[kThreads / kWave];
     __shared__ float rbox[32];
+    __shared__ float rsub[kBlocks][32];          // the waves' rows
+    __shared__ int nrow[kRowsPerGroup];          // candidates per row so far
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
     const int g = lane >> 4;
@@ -370,28 +552,35 @@ __global__ __launch_bounds__(kThreads) void knn_collect_kernel(
     const int64_t ic = i < n ? i : n - 1;
     const int64_t io = (i < n) ? (int64_t)perm[i] : -1;   // the point it holds
     const float t_i = (i < n) ? thr[io] : -1.0f;
+    const bool active = t_i >= 0.0f;
+    const float t_pass = active ? t_i : -INFINITY;
+    if (threadIdx.x < kRowsPerGroup)
+        nrow[threadIdx.x] = 0;
 
     // a workgroup with no active row has nothing to collect
-    if (__syncthreads_or(t_i >= 0.0f) == 0)
+    if (__syncthreads_or(active) == 0)
         return;
 
-    // the largest bound among the workgroup's rows, and their box
-    float tm = t_i;
+    // the largest bound among each wave's and the workgroup's rows (widened
+    // for the float32 gaps), and the boxes of the rows
+    const int64_t ntiles = (n + kTileCols - 1) / kTileCols;
+    const int64_t nsub = ntiles * kBlocks;
+    float wm = t_i;
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1)
-        tm = fmaxf(tm, __shfl_xor(tm, o, kWave));
+        wm = fmaxf(wm, __shfl_xor(wm, o, kWave));
     if (lane == 0)
-        wmax[wave] = tm;
+        wmax[wave] = (wm >= 0.0f) ? wm * (1.0f + 8e-6f) : -1.0f;
     if (threadIdx.x < 32)
-        rbox[threadIdx.x] = box[(int64_t)blockIdx.x * 32 + threadIdx.x];
+        rbox[threadIdx.x] = box[threadIdx.x * ntiles + blockIdx.x];
+    if (threadIdx.x < 32 * kBlocks)
+        rsub[threadIdx.x / 32][threadIdx.x % 32] =
+            sub[(threadIdx.x % 32) * nsub + (int64_t)blockIdx.x * kBlocks + threadIdx.x / 32];
     __syncthreads();
-    float tmax = wmax[0];
+    float cut = wmax[0];
 #pragma unroll
     for (int w = 1; w < kThreads / kWave; ++w)
-        tmax = fmaxf(tmax, wmax[w]);
-    // a tile is skipped when the squared gap between the boxes (float64,
-    // exact differences of float32 coordinates) exceeds every bound
-    const double cut = (double)tmax * (1.0 + 1e-12);
+        cut = fmaxf(cut, wmax[w]);
 
     float bop[KS];
 #pragma unroll
@@ -421,21 +610,15 @@ __global__ __launch_bounds__(kThreads) void knn_collect_kernel(
         }
     };
 
-    const int64_t ntiles = (n + kTileCols - 1) / kTileCols;
     for (int64_t c0 = 0; c0 < ntiles; c0 += kThreads) {
     // this chunk's tiles that may hold neighbours, in order
     bool pass = false;
     const int64_t tt = c0 + threadIdx.x;
     if (tt < ntiles) {
-        const float *bx = box + tt * 32;
-        double lb = 0.0;
-        for (int c = 0; c < d; ++c) {
-            double gap = (double)bx[c] - (double)rbox[16 + c];
-            const double g2 = (double)rbox[c] - (double)bx[16 + c];
-            gap = gap > g2 ? gap : g2;
-            if (gap > 0.0)
-                lb += gap * gap;
-        }
+        float lb = 0.0f;
+        for (int c = 0; c < d; ++c)
+            lb = box_gap2(box[c * ntiles + tt], box[(16 + c) * ntiles + tt], rbox[c],
+                          rbox[16 + c], lb);
         pass = !(lb > cut);
     }
     const unsigned long long bal = __ballot(pass);
@@ -453,6 +636,24 @@ __global__ __launch_bounds__(kThreads) void knn_collect_kernel(
     __syncthreads();
     if (cnt == 0)
         continue;                                // uniform over the workgroup
+    // which of a tile's 4 x 4 blocks may hold neighbours: 16 lanes a tile,
+    // lane 4 w + q the rows of wave w and the columns of block q
+    for (int u0 = 0; u0 < cnt; u0 += kThreads / 16) {
+        const int u = u0 + threadIdx.x / 16, w = (threadIdx.x / 4) % 4, q = threadIdx.x % 4;
+        bool near = false;
+        if (u < cnt) {
+            const int64_t b = (int64_t)tl[u] * kBlocks + q;
+            float lb = 0.0f;
+            for (int c = 0; c < d; ++c)
+                lb = box_gap2(sub[c * nsub + b], sub[(16 + c) * nsub + b], rsub[w][c],
+                              rsub[w][16 + c], lb);
+            near = !(lb > wmax[w]);
+        }
+        const unsigned long long mask = __ballot(near);
+        if (u < cnt && threadIdx.x % 16 == 0)
+            tm[u] = (unsigned short)(mask >> (lane & ~15));
+    }
+    __syncthreads();
     fetch((int64_t)tl[0] * kTileCols);
     commit(0);
     __syncthreads();
@@ -462,20 +663,25 @@ __global__ __launch_bounds__(kThreads) void knn_collect_kernel(
         if (u + 1 < cnt)
             fetch((int64_t)tl[u + 1] * kTileCols);
         const float *tile = reinterpret_cast<const float *>(xs[buf]) + g * kTileCols;
+        const int blocks = __builtin_amdgcn_readfirstlane((tm[u] >> (4 * wave)) & 15);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
+            if (!((blocks >> q) & 1))
+                continue;                        // uniform per wave
             floatx4 cacc = {0.0f, 0.0f, 0.0f, 0.0f};
             const float *ap = tile + ((16 * q + m) ^ (16 * g));
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 cacc = __builtin_amdgcn_mfma_f32_16x16x4f32(ap[4 * s * kTileCols], bop[s],
                                                             cacc, 0, 0, 0);
+            if (!(fminf(fminf(cacc[0], cacc[1]), fminf(cacc[2], cacc[3])) <= t_pass))
+                continue;
             const int64_t j0 = jt + 16 * q + 4 * g;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int64_t j = j0 + r;
-                if (t_i >= 0.0f && cacc[r] <= t_i && j < n && j != i) {
-                    const int c = atomicAdd(&count[io], 1);
+                if (cacc[r] <= t_pass && j < n && j != i) {
+                    const int c = atomicAdd(&nrow[16 * wave + m], 1);
                     if (c < kCap)
                         cand[io * kCap + c] = perm[j];
                 }
@@ -488,14 +694,64 @@ __global__ __launch_bounds__(kThreads) void knn_collect_kernel(
     }
     __syncthreads();                             // tl and xs are refilled next chunk
     }
+    if (g == 0 && active)
+        count[io] = nrow[16 * wave + m];
 }
 
 // ------------------------------------------------------------- 3. select
 
+// The k smallest (distance, index) of a row's `kept` candidates, P per lane
+// in registers: k rounds of a wave minimum, the winner's lane dropping it.
+// Returns the last one's distance.
+template <int P>
+__device__ __forceinline__ double select_row(const float *__restrict__ X, int d, int k,
+                                             int64_t i, int kept,
+                                             const int32_t *__restrict__ cand,
+                                             int32_t *__restrict__ nbr)
+{
+    const int lane = threadIdx.x % kWave;
+    double dv[P];
+    int32_t jv[P];
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+        const int e = u * kWave + lane;
+        jv[u] = (e < kept) ? cand[i * kCap + e] : INT32_MAX;
+        dv[u] = (e < kept) ? sq_dist64(X, d, i, jv[u]) : INFINITY;
+    }
+    double last = 0.0;
+    for (int t = 0; t < k; ++t) {
+        double bd = INFINITY;
+        int32_t bj = INT32_MAX;
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+            if (dv[u] < bd || (dv[u] == bd && jv[u] < bj)) {
+                bd = dv[u];
+                bj = jv[u];
+            }
+        argmin_step<32>(bd, bj);
+        argmin_step<16>(bd, bj);
+        argmin_step<8>(bd, bj);
+        argmin_step<4>(bd, bj);
+        argmin_step<2>(bd, bj);
+        argmin_step<1>(bd, bj);
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+            if (jv[u] == bj)
+                dv[u] = INFINITY, jv[u] = INT32_MAX;
+        if (lane == 0)
+            nbr[i * k + t] = bj;
+        last = bd;
+    }
+    return last;
+}
+
 // A wave per active row: float64 squared distances of the kept candidates
-// (at most kCap, 32 per lane, in registers), then k rounds of a wave
-// argmin over (distance, index).  nbr[i k + t] are the k nearest in order;
-// kth[i] is the k-th distance; a row whose list overflowed is flagged.
+// (at most kCap), then k rounds of a wave argmin over (distance, index).
+// nbr[i k + t] are the k nearest in order; kth[i] is the k-th distance; a
+// row whose list overflowed is flagged.  Every round visits each lane's
+// registers, so a row takes as few as its list needs: 2, 4, 8 or all 32 per
+// lane (n = 2M, k = 32, 32 per lane always: 57 ms with 165
+// candidates a row on average; 19 by their number; 15 with 70).
 __global__ __launch_bounds__(kThreads) void knn_select_kernel(
     const float *__restrict__ X, int64_t n, int d, int k, const int *__restrict__ active,
     int *__restrict__ count, const int32_t *__restrict__ cand, int32_t *__restrict__ nbr,
@@ -507,46 +763,15 @@ __global__ __launch_bounds__(kThreads) void knn_select_kernel(
         return;                                             // uniform per wave
     const int cnt = count[i];
     const int kept = cnt < kCap ? cnt : kCap;
-    double dv[kPerLane];
-    int32_t jv[kPerLane];
-#pragma unroll
-    for (int u = 0; u < kPerLane; ++u) {
-        const int e = u * kWave + lane;
-        if (e < kept) {
-            jv[u] = cand[i * kCap + e];
-            dv[u] = sq_dist64(X, d, i, jv[u]);
-        } else {
-            jv[u] = INT32_MAX;
-            dv[u] = INFINITY;
-        }
-    }
-    double last = 0.0;
-    for (int t = 0; t < k; ++t) {
-        double bd = INFINITY;
-        int32_t bj = INT32_MAX;
-#pragma unroll
-        for (int u = 0; u < kPerLane; ++u)
-            if (dv[u] < bd || (dv[u] == bd && jv[u] < bj)) {
-                bd = dv[u];
-                bj = jv[u];
-            }
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) {
-            const double od = __shfl_xor(bd, o, kWave);
-            const int32_t oj = __shfl_xor(bj, o, kWave);
-            if (od < bd || (od == bd && oj < bj)) {
-                bd = od;
-                bj = oj;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kPerLane; ++u)
-            if (jv[u] == bj)
-                dv[u] = INFINITY, jv[u] = INT32_MAX;
-        if (lane == 0)
-            nbr[i * k + t] = bj;
-        last = bd;
-    }
+    double last;
+    if (kept <= 2 * kWave)
+        last = select_row<2>(X, d, k, i, kept, cand, nbr);
+    else if (kept <= 4 * kWave)
+        last = select_row<4>(X, d, k, i, kept, cand, nbr);
+    else if (kept <= 8 * kWave)
+        last = select_row<8>(X, d, k, i, kept, cand, nbr);
+    else
+        last = select_row<kPerLane>(X, d, k, i, kept, cand, nbr);
     if (lane == 0) {
         kth[i] = last;
         if (cnt > kCap || last == INFINITY)
@@ -700,26 +925,28 @@ KnnLayout knn_layout(int64_t n, int32_t k)
 }
 
 template <int D>
-void launch_bound(int KT, const float *X, const int32_t *perm, int64_t n, int k, float *tau,
-                  hipStream_t s)
+void launch_bound(int KT, const float *X, const int32_t *perm, int64_t n, int k,
+                  const int32_t *near, float *tau, hipStream_t s)
 {
-    const dim3 grid((unsigned)((n + kThreads - 1) / kThreads));
+    const int64_t nt = (n + kTileCols - 1) / kTileCols;
+    constexpr int kRowTiles = kThreads / kWave;
+    const dim3 grid((unsigned)((nt + kRowTiles - 1) / kRowTiles));
     switch (KT) {
     case 8:
-        hipLaunchKernelGGL((knn_bound_kernel<D, 8>), grid, dim3(kThreads), 0, s, X, perm, n, k,
-                           tau);
+        hipLaunchKernelGGL((knn_bound_kernel<D, 8>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
+                           near, tau);
         break;
     case 16:
-        hipLaunchKernelGGL((knn_bound_kernel<D, 16>), grid, dim3(kThreads), 0, s, X, perm, n,
-                           k, tau);
+        hipLaunchKernelGGL((knn_bound_kernel<D, 16>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
+                           near, tau);
         break;
     case 32:
-        hipLaunchKernelGGL((knn_bound_kernel<D, 32>), grid, dim3(kThreads), 0, s, X, perm, n,
-                           k, tau);
+        hipLaunchKernelGGL((knn_bound_kernel<D, 32>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
+                           near, tau);
         break;
     default:
-        hipLaunchKernelGGL((knn_bound_kernel<D, 64>), grid, dim3(kThreads), 0, s, X, perm, n,
-                           k, tau);
+        hipLaunchKernelGGL((knn_bound_kernel<D, 64>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
+                           near, tau);
         break;
     }
 }
@@ -775,14 +1002,23 @@ hipError_t run_knn_graph(const float *X, int64_t n, int d, int k, float sigma,
                        (const int32_t *)perm, n, np, d, 4 * KS, xa, xb, norm2);
     const int64_t ntiles = np / kTileCols;
     float *box = (float *)(w + L.box);
+    // the sort's keys are done with until the edges: the blocks' boxes and
+    // the near tiles take their place (10 bytes a point and at most 256 more,
+    // of 40 or more)
+    float *sub = (float *)(w + L.keyA);
+    int32_t *near = (int32_t *)(w + L.keyA + al(ntiles * kBlocks * 32 * 4));
+    if (L.keyA + al(ntiles * kBlocks * 32 * 4) + (size_t)ntiles * kNear * 4 > L.permA)
+        return hipErrorInvalidValue;             // not reached
     hipLaunchKernelGGL(tile_box_kernel, dim3((unsigned)((ntiles * 16 + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, X, (const int32_t *)perm, n, d, ntiles, box);
+                       dim3(kThreads), 0, s, X, (const int32_t *)perm, n, d, ntiles, box, sub);
+    hipLaunchKernelGGL(near_tiles_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, s,
+                       (const float *)box, ntiles, d, near);
 
     // 1. bound, over the Morton neighbours
     const int KT = k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 ? 32 : 64;
 #define GPIC_BOUND(D)                                                          \
     case D:                                                                    \
-        launch_bound<D>(KT, X, perm, n, k, tau, s);                            \
+        launch_bound<D>(KT, X, perm, n, k, near, tau, s);                      \
         break;
     switch (d) {
         GPIC_BOUND(1) GPIC_BOUND(2) GPIC_BOUND(3) GPIC_BOUND(4) GPIC_BOUND(5) GPIC_BOUND(6)
@@ -792,6 +1028,10 @@ hipError_t run_knn_graph(const float *X, int64_t n, int d, int k, float sigma,
         return hipErrorInvalidValue;
     }
 #undef GPIC_BOUND
+    hipLaunchKernelGGL(refine_bound_kernel, dim3((unsigned)ntiles * kRefineParts),
+                       dim3(kThreads), 0, s, X,
+                       (const int32_t *)perm, (const float *)box, n, ntiles, d, k,
+                       (const int *)nullptr, tau);
     hipLaunchKernelGGL(threshold_kernel, dim3(rows_grid), dim3(kThreads), 0, s, tau,
                        (const double *)nullptr, norm2, maxn, n, d, 4 * KS,
                        (const int *)nullptr, thr);
@@ -803,11 +1043,11 @@ hipError_t run_knn_graph(const float *X, int64_t n, int d, int k, float sigma,
         const dim3 cgrid((unsigned)((n + kRowsPerGroup - 1) / kRowsPerGroup));
         if (KS <= 3)
             hipLaunchKernelGGL(knn_collect_kernel<3>, cgrid, dim3(kThreads), 0, s, xa, np,
-                               xb, n, d, (const int32_t *)perm, (const float *)box, thr, count,
+                               xb, n, d, (const int32_t *)perm, (const float *)box, (const float *)sub, thr, count,
                                cand);
         else
             hipLaunchKernelGGL(knn_collect_kernel<5>, cgrid, dim3(kThreads), 0, s, xa, np,
-                               xb, n, d, (const int32_t *)perm, (const float *)box, thr, count,
+                               xb, n, d, (const int32_t *)perm, (const float *)box, (const float *)sub, thr, count,
                                cand);
         hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(kThreads), 0, s, flags, (int64_t)1,
                            0);
@@ -831,6 +1071,10 @@ hipError_t run_knn_graph(const float *X, int64_t n, int d, int k, float sigma,
         }
         hipLaunchKernelGGL(knn_rearm_kernel, dim3(rows_grid), dim3(kThreads), 0, s, n,
                            count, (const double *)kth, active);
+        hipLaunchKernelGGL(refine_bound_kernel, dim3((unsigned)ntiles * kRefineParts),
+                       dim3(kThreads), 0, s, X,
+                           (const int32_t *)perm, (const float *)box, n, ntiles, d, k,
+                           (const int *)active, tau);
         hipLaunchKernelGGL(threshold_kernel, dim3(rows_grid), dim3(kThreads), 0, s, tau,
                            (const double *)kth, norm2, maxn, n, d, 4 * KS,
                            (const int *)active, thr);

@@ -732,6 +732,20 @@ def test_knn_graph_parity(g, orc, n, d, k, shift):
     _check_knn(g, orc, X, k, 1.0)
 
 
+@pytest.mark.parametrize("n,d,k", [(16449, 8, 64), (20011, 5, 20), (17000, 16, 32)])
+def test_knn_graph_scattered(g, orc, n, d, k):
+    """Tight clusters and points scattered between them: row tiles that
+    straddle clusters (bounds refined row by row), rows whose lists overflow
+    (collected again), more than 256 tiles, sizes off the tile and block
+    edges."""
+    rng = np.random.default_rng(n)
+    C = 6.0 * rng.standard_normal((7, d))
+    X = C[rng.integers(0, 7, n)] + 0.05 * rng.standard_normal((n, d))
+    X[rng.permutation(n)[:300]] = 8.0 * rng.standard_normal((300, d))
+    print(f"knn graph scattered n={n} d={d} k={k}", flush=True)
+    _check_knn(g, orc, X.astype(np.float32), k, 1.0)
+
+
 def test_knn_graph_ties(g, orc):
     """Integer lattice (exact distance ties go to the smaller index)."""
     grid = np.arange(12, dtype=np.float32)
