@@ -53,7 +53,15 @@ constexpr int kWaves = kThreads / kWave;
 // 1,024 cells costs 0.1-0.3 ms more, of 256 leaves wider windows.  Below
 // 8,192 values the full programme is two or three levels a layer and the
 // scratch holds few cells (n = 5,000, k = 24: 0.7-1.9 ms against 1.3).
+// With few clusters the full programme is short as well, three launches a
+// level for each layer but the last, and below 2^18 values it has three
+// levels: n = 10,000, k = 3, 5, 7, 10: 0.40, 0.50, 0.61, 0.76 ms against 0.47,
+// 0.50, 0.56, 0.64; n = 50,000, k = 3, 6, 8: 0.43, 0.62, 0.72 against 0.48,
+// 0.60, 0.70.  From 2^18 values it has six or more: n = 270,000, k = 3: 0.72
+// against 0.68; n = 2M, k = 3: 1.35 against 1.03.
 constexpr int64_t kFromN = 8192;
+constexpr int64_t kLargeN = (int64_t)1 << 18;
+constexpr int kFewSmall = 7;
 constexpr int kFirst = 512;              // cells of the first round
 constexpr int kMaxPer = 1024;            // cells per layer of a window later
 constexpr int kMaxMerged = 8;            // a window of several layers: up to this many times as many
@@ -711,7 +719,7 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
                           size_t ws_bytes, int64_t *first, hipStream_t s, int *solved)
 {
     *solved = 0;
-    if (ke < 3 || ke > kMaxClusters || n < kFromN)
+    if (ke < (n < kLargeN ? kFewSmall : 3) || ke > kMaxClusters || n < kFromN)
         return hipSuccess;
     // cells of the first round, and rows for merged windows: as many as are
     // useful and the scratch holds; with few per cluster the windows would

@@ -416,12 +416,12 @@ def test_kmeans1d_unclustered(g, orc, n, k):
     check_kmeans(v, out, orc.kmeans1d(v, k, "dc"))
 
 
-@pytest.mark.parametrize("n,k", [(8191, 3), (8192, 3), (8192, 24), (20011, 10), (60000, 24),
-                                 (300007, 12)])
+@pytest.mark.parametrize("n,k", [(8191, 7), (8192, 7), (8192, 24), (20011, 10), (60000, 24),
+                                 (262144, 3), (300007, 12)])
 @pytest.mark.parametrize("shape", ["normal", "tail", "tight", "gaps", "ties", "offset"])
 def test_kmeans1d_windows(g, orc, n, k, shape):
-    """From 8,192 values the layers are solved inside windows around the
-    optimal cuts.  Shapes that stretch the bounds: dense and sparse by turns,
+    """From 8,192 values and 7 clusters (262,144 values: 3) the layers are
+    solved inside windows around the optimal cuts.  Shapes that stretch the bounds: dense and sparse by turns,
     clusters 1e-9 wide (values equal to the rounding of the prefix sums),
     half as many clusters as k, few distinct values, a large offset."""
     rng = np.random.default_rng(n + 31 * k)
