@@ -187,6 +187,124 @@ __global__ __launch_bounds__(kScanThreads) void scan_tiles_kernel(
     }
 }
 
+// Up to one tile of values: the keys, their sort (a bitonic network over
+// (key, input position) in LDS, the order of the radix passes), the sorted
+// values, run starts, mean and prefix sums in one launch of one workgroup
+// instead of seven; every sum in the order of the kernels it stands for
+// (256 threads, tile offset 0).  Bound by its barriers, about 70 for 1,000
+// values: 25 us there, 42 and the gaps between launches before (600 values,
+// k = 3, the whole call: 205 -> 155 us).
+constexpr int kSmallThreads = 1024;
+__global__ __launch_bounds__(kSmallThreads) void small_prepare_kernel(
+    const double *__restrict__ v, int n, int P, int32_t *__restrict__ idx,
+    double *__restrict__ sv, int32_t *__restrict__ run, KmScalars *__restrict__ sc,
+    double2 *__restrict__ SS)
+{
+    __shared__ uint64_t key[kTile];
+    __shared__ int32_t pos[kTile];
+    __shared__ double a1[kThreads], a2[kThreads];
+    __shared__ double red[2][kThreads / kWave];
+    const int tid = threadIdx.x;
+    for (int i = tid; i < P; i += kSmallThreads) {
+        key[i] = (i < n) ? to_key(v[i]) : ~0ull;
+        pos[i] = i;
+    }
+    __syncthreads();
+    for (int size = 2; size <= P; size <<= 1) {
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            for (int t = tid; t < P / 2; t += kSmallThreads) {
+                const int lo = 2 * t - (t & (stride - 1));
+                const int hi = lo + stride;
+                const bool up = (lo & size) == 0;
+                const uint64_t ka = key[lo], kb = key[hi];
+                const int32_t pa = pos[lo], pb = pos[hi];
+                const bool gt = (ka > kb) || (ka == kb && pa > pb);
+                if (gt == up) {
+                    key[lo] = kb;
+                    key[hi] = ka;
+                    pos[lo] = pb;
+                    pos[hi] = pa;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    for (int i = tid; i < n; i += kSmallThreads) {
+        idx[i] = pos[i];
+        sv[i] = from_key(key[i]);
+        run[i] = (i == 0) || (key[i - 1] != key[i]);
+    }
+    const bool low = tid < kThreads;             // the summing threads
+    double s = 0.0, r = 0.0;
+    if (low)
+        for (int it = 0; it < kItems; ++it) {
+            const int i = it * kThreads + tid;
+            if (i < n) {
+                s += from_key(key[i]);
+                r += (i == 0) || (key[i - 1] != key[i]);
+            }
+        }
+    s = wave_sum(s);
+    r = wave_sum(r);
+    if (low && tid % kWave == 0) {
+        red[0][tid / kWave] = s;
+        red[1][tid / kWave] = r;
+    }
+    __syncthreads();
+    double ts = 0.0, tr = 0.0;
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w) {
+        ts += red[0][w];
+        tr += red[1][w];
+    }
+    const double mu = ts / (double)n;
+    if (tid == 0) {
+        sc->mean = mu;
+        sc->distinct = tr;
+        SS[0] = double2{0.0, 0.0};
+    }
+    const int b = tid * kItems;
+    double i1 = 0.0, i2 = 0.0;
+    if (low)
+        for (int it = 0; it < kItems; ++it)
+            if (b + it < n) {
+                const double u = from_key(key[b + it]) - mu;
+                i1 += u;
+                i2 += u * u;
+            }
+    // block_scan2 over the first kThreads threads
+    if (low) {
+        a1[tid] = i1;
+        a2[tid] = i2;
+    }
+    __syncthreads();
+    for (int off = 1; off < kThreads; off <<= 1) {
+        const double y1 = (low && tid >= off) ? a1[tid - off] : 0.0;
+        const double y2 = (low && tid >= off) ? a2[tid - off] : 0.0;
+        __syncthreads();
+        i1 += y1;
+        i2 += y2;
+        if (low) {
+            a1[tid] = i1;
+            a2[tid] = i2;
+        }
+        __syncthreads();
+    }
+    if (!low)
+        return;
+    double r1 = tid > 0 ? a1[tid - 1] : 0.0;
+    double r2 = tid > 0 ? a2[tid - 1] : 0.0;
+    for (int it = 0; it < kItems; ++it) {
+        const int i = b + it;
+        if (i < n) {
+            const double u = from_key(key[i]) - mu;
+            r1 += u;
+            r2 += u * u;
+            SS[i + 1] = double2{r1, r2};
+        }
+    }
+}
+
 // SS[i+1] = (S1[i+1], S2[i+1]) = tile offset + in-tile running sums (each
 // thread walks its kItems elements after an exclusive scan of the thread
 // totals); the two sums of a position sit together, one 16-byte load.
@@ -459,8 +577,11 @@ __global__ __launch_bounds__(1024) void level_scan_kernel(
         ts[threadIdx.x] = t;
         __syncthreads();
         if (threadIdx.x == 0) {
+            // only the threads that hold blocks (walking all 1,024 sums was 17
+            // us of a 1,000-value call)
+            const int used = (int)((nb + per - 1) / per);
             int32_t run = 0;
-            for (int u = 0; u < 1024; ++u) {
+            for (int u = 0; u < used; ++u) {
                 const int32_t x = ts[u];
                 ts[u] = run;
                 run += x;
@@ -948,6 +1069,14 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     double *costs = (double *)(w + L.costs);
     const int64_t nt = tiles(n);
 
+    if (n <= kTile) {
+        int P = 1;
+        while (P < n)
+            P <<= 1;
+        hipLaunchKernelGGL(small_prepare_kernel, dim3(1), dim3(kSmallThreads), 0, s, v, (int)n,
+                           P, idxA, sv, run, sc, SS);
+        GPIC_TRY(hipGetLastError());
+    } else {
     // 1. radix sort
     hipLaunchKernelGGL(make_keys_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
                        v, n, keyA, idxA);
@@ -964,6 +1093,7 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s, sv,
                        n, sc, t1, t2, SS);
     GPIC_TRY(hipGetLastError());
+    }
     KmScalars hsc{};
     GPIC_TRY(hipMemcpyAsync(&hsc, sc, sizeof(hsc), hipMemcpyDeviceToHost, s));
     GPIC_TRY(hipStreamSynchronize(s));
@@ -1046,16 +1176,19 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
         RowEntry *ent = (RowEntry *)(w + L.ent), *list = (RowEntry *)(w + L.list);
         int32_t *lr = (int32_t *)(w + L.lr), *bh = (int32_t *)(w + L.bh);
         int32_t *lbase = (int32_t *)(w + L.lbase);
-        if (F == kFSmall)
+        // two clusters need the last layer's one row only
+        if (ke > 2 && F == kFSmall)
             hipLaunchKernelGGL(row_level_kernel<kFSmall>, dim3(blocks_for(n)), dim3(kThreads),
                                0, s, (int32_t)n, levels, ent, lr, bh);
-        else
+        else if (ke > 2)
             hipLaunchKernelGGL(row_level_kernel<kFLarge>, dim3(blocks_for(n)), dim3(kThreads),
                                0, s, (int32_t)n, levels, ent, lr, bh);
-        hipLaunchKernelGGL(level_scan_kernel, dim3(1), dim3(1024), 0, s, bh,
-                           (int64_t)blocks_for(n), levels, lbase);
-        hipLaunchKernelGGL(level_scatter_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
-                           (int32_t)n, ent, lr, bh, lbase, list);
+        if (ke > 2) {
+            hipLaunchKernelGGL(level_scan_kernel, dim3(1), dim3(1024), 0, s, bh,
+                               (int64_t)blocks_for(n), levels, lbase);
+            hipLaunchKernelGGL(level_scatter_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
+                               (int32_t)n, ent, lr, bh, lbase, list);
+        }
         int g = 0;                                 // levels run so far
         for (int c = 1; c < ke; ++c) {
             int32_t *oc = opt + (int64_t)c * n;

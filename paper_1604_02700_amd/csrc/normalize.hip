@@ -152,6 +152,35 @@ __global__ __launch_bounds__(kThreads) void start_vector_kernel(
         v0[i] = degree[i] / total;
 }
 
+// The three above in one launch where one workgroup sums every degree (n <=
+// kChunk): the same sums in the same order.
+__global__ __launch_bounds__(kThreads) void small_start_kernel(
+    const double *__restrict__ degree, int64_t n, StartWs *__restrict__ st,
+    int64_t *__restrict__ n_zero, double *__restrict__ v0)
+{
+    __shared__ double red[kThreads / kWave];
+    double s = 0.0, z = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += kThreads) {
+        const double x = degree[i];
+        s += x;
+        z += (x == 0.0) ? 1.0 : 0.0;
+    }
+    const double total = block_sum<kThreads>(s, red);
+    const double tz = block_sum<kThreads>(z, red);
+    const int bad = !(total > 0.0) || !isfinite(total);
+    if (threadIdx.x == 0) {
+        st->total = total;
+        st->nzero = (int64_t)tz;
+        st->bad = bad;
+        if (n_zero != nullptr)
+            *n_zero = (int64_t)tz;
+    }
+    if (bad)
+        return;
+    for (int64_t i = threadIdx.x; i < n; i += kThreads)
+        v0[i] = degree[i] / total;
+}
+
 // row_ptr[0] == 0, row_ptr[n] == nnz, row_ptr non-decreasing, every column
 // in [0, n).  Any violation sets *flag.
 __global__ __launch_bounds__(kThreads) void csr_check_kernel(
@@ -248,13 +277,18 @@ hipError_t launch_start_vector(const double *degree, int64_t n, double *v0,
     StartWs *st = reinterpret_cast<StartWs *>(base);
     double *psum = reinterpret_cast<double *>(base + 256);
     int64_t *pzero = reinterpret_cast<int64_t *>(base + 256 + nb * 8);
-    hipLaunchKernelGGL(degree_partials_kernel, dim3((unsigned)nb), dim3(kThreads),
-                       0, s, degree, n, psum, pzero);
-    hipLaunchKernelGGL(degree_total_kernel, dim3(1), dim3(1024), 0, s, psum,
-                       pzero, nb, st, n_zero);
-    hipLaunchKernelGGL(start_vector_kernel,
-                       dim3((unsigned)((n + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, degree, n, st, v0);
+    if (nb == 1) {
+        hipLaunchKernelGGL(small_start_kernel, dim3(1), dim3(kThreads), 0, s, degree, n, st,
+                           n_zero, v0);
+    } else {
+        hipLaunchKernelGGL(degree_partials_kernel, dim3((unsigned)nb), dim3(kThreads),
+                           0, s, degree, n, psum, pzero);
+        hipLaunchKernelGGL(degree_total_kernel, dim3(1), dim3(1024), 0, s, psum,
+                           pzero, nb, st, n_zero);
+        hipLaunchKernelGGL(start_vector_kernel,
+                           dim3((unsigned)((n + kThreads - 1) / kThreads)),
+                           dim3(kThreads), 0, s, degree, n, st, v0);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
