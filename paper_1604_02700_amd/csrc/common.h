@@ -253,7 +253,8 @@ hipError_t launch_spmv_blocked(const CsrBlocked &B, const double *v, double *y,
 // `bits` bits (a multiple of 8), with an optional int32 payload (idxA and
 // idxB null for keys alone).  The sorted arrays end in keyA / idxA (the
 // pointers are swapped per pass).  hist: radix_hist_bytes(n) bytes, hsum:
-// radix_hsum_bytes(n) bytes.
+// radix_hsum_bytes(n) bytes.  With small_tiles (few keys go in small
+// tiles) they hold at least 2n bytes each, n >= 4,096.
 size_t radix_hist_bytes(int64_t n);
 size_t radix_hsum_bytes(int64_t n);
 // in-place exclusive scan of m uint32 values (total < 2^32); sums:
@@ -262,7 +263,7 @@ size_t scan_sums_bytes(int64_t m);
 hipError_t exclusive_scan_u32(uint32_t *a, int64_t m, uint32_t *sums, hipStream_t s);
 hipError_t radix_sort_u64(uint64_t *&keyA, int32_t *&idxA, uint64_t *&keyB, int32_t *&idxB,
                           int64_t n, int bits, uint32_t *hist, uint32_t *hsum,
-                          hipStream_t s);
+                          hipStream_t s, bool small_tiles = false);
 
 // knn.hip -- exact kNN graph (d <= 16, k <= 64, 2 n k < 2^32); synchronises.
 // *status_host = 1 when the candidate bounds failed to converge (nothing

@@ -1049,7 +1049,6 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     uint64_t *keyA = (uint64_t *)(w + L.keyA), *keyB = (uint64_t *)(w + L.keyB);
     int32_t *idxA = (int32_t *)(w + L.idxA), *idxB = (int32_t *)(w + L.idxB);
     uint32_t *hist = (uint32_t *)(w + L.hist);
-    uint32_t *hsum = (uint32_t *)(w + L.hsum);
     double *sv = (double *)(w + L.sv);
     int32_t *run = (int32_t *)(w + L.run);
     double *t1 = (double *)(w + L.t1), *t2 = (double *)(w + L.t2);
@@ -1080,7 +1079,10 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     // 1. radix sort
     hipLaunchKernelGGL(make_keys_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
                        v, n, keyA, idxA);
-    GPIC_TRY(radix_sort_u64(keyA, idxA, keyB, idxB, n, 64, hist, hsum, s));
+    // (its histogram in the sorted values' place and its block sums in the
+    // prefix sums', 8n and 16n bytes that are written after the sort)
+    GPIC_TRY(radix_sort_u64(keyA, idxA, keyB, idxB, n, 64, (uint32_t *)sv, (uint32_t *)SS, s,
+                            true));
     GPIC_TRY(hipGetLastError());
 
     // 2. values, runs, mean, prefix sums

@@ -385,6 +385,7 @@ def test_pic_cosine_parity(g, orc, name):
                                      (64, 8, False), (65, 8, False), (66, 8, True),
                                      (1000, 4, False), (4097, 10, False),
                                      (4097, 10, True), (4225, 20, True),
+                                     (65536, 3, False), (65537, 4, True),
                                      (4291, 7, False), (50000, 10, False),
                                      (20000, 50, True), (274626, 30, False),
                                      (500000, 50, False), (262143, 20, False),
@@ -396,7 +397,8 @@ def test_kmeans1d_parity(g, orc, n, k, dup):
     a level), the switch between the two (262,143 / 262,144), fewer
     distinct values than k (300,001 values rounded to about 100 integers,
     k = 200), and k = n or n - 1 (the last layer's one row has a single
-    split point, or two, with a finite cost)."""
+    split point, or two, with a finite cost), the sort's small and large
+    tiles (65,536 / 65,537)."""
     rng = np.random.default_rng(n + k)
     m = max(1, min(k, n))
     centres = np.sort(rng.uniform(0, 100, size=m))
