@@ -574,7 +574,9 @@ __global__ __launch_bounds__(kThreads) void windows_kernel(View V)
     __syncthreads();
     if (threadIdx.x != 0)
         return;
-    int fail = 0;
+    // squares that overflow leave no bound that means anything: every row is
+    // computed instead
+    int fail = !(V.SS[V.n].y < INFINITY);
     for (int c = 1; c < V.ke; ++c)
         fail |= lo[c] > hi[c];
     for (int c = V.ke - 2; c >= 1; --c)
