@@ -1241,6 +1241,8 @@ __global__ __launch_bounds__(kThreads, 2) void affinity_valu_sym_kernel(
 
 // ------------------------------------------------------------- dispatch
 
+constexpr int kValuRows = 8;               // rows of an affinity_valu_kernel workgroup
+
 bool use_mfma(int d) { return d >= 16 && d <= 128; }
 
 constexpr int kMaxNch = 4;                   // 32-coordinate chunks for d <= 128
@@ -1446,7 +1448,7 @@ hipError_t dispatch(const float *X, int64_t n, int d, float c, float *A,
         return hipGetLastError();
     }
     const dim3 block(kThreads);
-    constexpr int RB = 8;
+    constexpr int RB = kValuRows;
     const dim3 grid((unsigned)((n + RB - 1) / RB));
 #define GPIC_VALU(D)                                                           \
     case D:                                                                    \
@@ -1475,7 +1477,7 @@ hipError_t dispatch_cosine(const float *X, int64_t n, int d, float *A, int64_t l
     hipLaunchKernelGGL(inv_norm_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, s, X, n, d, rinv);
     const dim3 block(kThreads);
-    constexpr int RB = 8;
+    constexpr int RB = kValuRows;
     const dim3 grid((unsigned)((n + RB - 1) / RB));
     StopCtl none{};
 #define GPIC_COS(D)                                                             \
@@ -1531,12 +1533,16 @@ size_t affinity_ws(int64_t n)
                     al256((int64_t)kMaxChunks * n * 8));
 }
 
+// |y| partial sums of one fused product: a workgroup each of the launch that
+// ends it.  Asked in the order in which launch_fused_apply chooses, whose
+// reduction takes its grid from here, so that a loop never adds a partial
+// that no workgroup wrote.
 int64_t fused_blocks(int64_t n, int d)
 {
-    if (!use_mfma(d))
-        return (n + 7) / 8;
     if (fused_sym(n, d))
         return (n + kThreads - 1) / kThreads;        // fused_sym_reduce workgroups
+    if (!use_mfma(d))
+        return (n + kValuRows - 1) / kValuRows;      // affinity_valu_kernel workgroups
     int64_t chunk_cols;
     int nchunks;
     chunking(n, &chunk_cols, &nchunks);
@@ -1634,7 +1640,7 @@ hipError_t launch_fused_apply(const float *X, int64_t n, int d, float c,
 #undef GPIC_MFMA
     G = rows_per_group(kApplySym, nch_for(d));
     }
-    hipLaunchKernelGGL(fused_sym_reduce_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)),
+    hipLaunchKernelGGL(fused_sym_reduce_kernel, dim3((unsigned)fused_blocks(n, d)),
                        dim3(kThreads), 0, s, w.part, nchunks, chunk_cols, colpart, n, G, degree,
                        y, partial, ctl, uc);
     return hipGetLastError();

@@ -35,6 +35,27 @@ def _t(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
 
 
+@pytest.fixture
+def scratch(g, monkeypatch):
+    """scratch(x): from now on every buffer the binding allocates (workspaces
+    and outputs) holds the float64 x throughout before the call."""
+    class Filled:
+        def __init__(self, x):
+            self.x = x
+
+        def __getattr__(self, name):
+            return getattr(torch, name)
+
+        def empty(self, *a, **kw):
+            t = torch.empty(*a, **kw)
+            if t.is_cuda and t.numel() * t.element_size() >= 8:
+                b = t.view(-1).view(torch.uint8)
+                b[:b.numel() // 8 * 8].view(torch.float64).fill_(self.x)
+            return t
+
+    return lambda x: monkeypatch.setattr(g, "torch", Filled(x))
+
+
 # --------------------------------------------------------------- affinity
 @pytest.mark.parametrize("n,d", [(2, 2), (3, 1), (63, 2), (64, 3), (65, 15),
                                  (1000, 2), (1023, 5), (130, 16), (257, 17),
@@ -516,6 +537,48 @@ def test_fused_symmetric_few_dimensions(g, orc, n, d):
     ones = torch.ones(n, dtype=torch.float64, device=DEV)
     y1 = g.gpic_matvec_fused(_t(X), sigma, deg, ones).cpu().numpy()
     np.testing.assert_allclose(y1, 1.0, rtol=1e-12)
+
+
+@pytest.mark.parametrize("n,d", [(9999, 3), (10000, 1), (10241, 8), (12037, 5), (20011, 15),
+                                 (20011, 16)])
+def test_fused_loop_few_dimensions(g, orc, scratch, n, d):
+    """The loop over the operator that evaluates each pair once, its
+    workspace full of large values that no kernel of it wrote: five updates
+    against the oracle (relative L1 as in test_fused_parity), and to
+    convergence against the same loop over single products (the same
+    float32 affinities; the float64 sums of n / 256 or n / 8 partials differ
+    from torch's by at most n 2^-53 = 2e-12 relatively, per update)."""
+    X = _pts(n, d, 70 + d, scale=1.2)
+    sigma = np.float32(0.5 * np.sqrt(d))
+    eps = 1e-5 / n
+    scratch(1e300)
+    print(f"fused loop n={n} d={d}", flush=True)
+    deg, v0, _ = g.gpic_degree_fused(_t(X), sigma)
+    v = v0.clone()
+    g.gpic_power_iterate_fused(_t(X), sigma, deg, v, None, "fixed", 5)
+    assert float(v.abs().sum()) == pytest.approx(1.0, rel=1e-12)
+    dr, v0r, _ = orc.degree_onthefly(X, sigma)
+    ref = orc.power_iterate_onthefly(X, sigma, dr, v0r, "fixed", 5)
+    assert rel_l1(v.cpu().numpy(), ref.v) <= 1e-4
+
+    w, delta, stats = v0.clone(), v0.clone(), []
+    for _ in range(60):
+        y = g.gpic_matvec_fused(_t(X), sigma, deg, w)
+        new = y / y.abs().sum()
+        dn = (new - w).abs()
+        stats.append(float((dn - delta).abs().max()))
+        w, delta = new, dn
+        if stats[-1] <= eps:
+            break
+    v, dv = v0.clone(), v0.clone()
+    out = g.gpic_power_iterate_fused(_t(X), sigma, deg, v, dv, "converge", 60, eps)
+    assert out.iterations == len(stats) and out.converged == (stats[-1] <= eps)
+    np.testing.assert_allclose(out.stats, stats, rtol=1e-6, atol=1e-9 / n)
+    assert rel_l1(v.cpu().numpy(), w.cpu().numpy()) <= 1e-10
+    np.testing.assert_allclose(dv.cpu().numpy(), delta.cpu().numpy(), rtol=1e-6, atol=1e-10 / n)
+    job = g.pic_fused(_t(X), sigma, 4, "converge", 60, eps)
+    assert job.pi.iterations == len(stats)
+    assert rel_l1(job.pi.v.cpu().numpy(), w.cpu().numpy()) <= 1e-10
 
 
 def test_fused_few_dimensions_far_point(g):
