@@ -10,8 +10,11 @@
 //   1. bound: the points are put in Morton order of their quantised centred
 //      coordinates and cut into tiles of 64 consecutive ones; for every row,
 //      the k-th smallest float32 squared distance to the points of the 32
-//      tiles whose boxes are centred nearest to its own tile's, which bounds
-//      the true k-th neighbour distance from above;
+//      tiles whose boxes are centred nearest to its own tile's and of the
+//      tiles next to it in Morton order, or, for rows whose bound is wide
+//      against their tile's smallest, of the 32 tiles nearest to the row
+//      itself; the k-th distance to any points bounds the true k-th
+//      neighbour distance from above;
 //   2. collect: squared distances on the fp32 matrix cores (Gram form over
 //      the centred points augmented as [x_j, |x_j|^2, 1] .
 //      [-2 x_i, 1, |x_i|^2]), appending every j that passes the row's bound
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void near_tiles_kernel(const float *__res
 template <int D, int KT>
 __global__ __launch_bounds__(kThreads) void knn_bound_kernel(
     const float *__restrict__ X, const int32_t *__restrict__ perm, int64_t n, int64_t nt, int k,
-    const int32_t *__restrict__ near, float *__restrict__ tau)
+    const int32_t *__restrict__ near, float *__restrict__ tau, float *__restrict__ tmin)
 {
     __shared__ float tile[kThreads / kWave][kWave * D];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -184,21 +187,29 @@ __global__ __launch_bounds__(kThreads) void knn_bound_kernel(
             }
         }
     }
-    if (p < n) {
-        float t = best[0];
+    float t = best[0];
 #pragma unroll
-        for (int u = 1; u < KT; ++u)
-            if (u == k - 1)
-                t = best[u];
+    for (int u = 1; u < KT; ++u)
+        if (u == k - 1)
+            t = best[u];
+    if (p < n)
         tau[i] = t;
-    }
+    else
+        t = INFINITY;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1)
+        t = fminf(t, __shfl_xor(t, o, kWave));
+    if (lane == 0)
+        tmin[row] = t;
 }
 
 // The bound again for single rows, from the tiles nearest to the row itself:
 // four workgroups per row tile take, one after another, the rows whose
 // bound is more than kWide times the tile's smallest (flags null: before the
 // first collection; the rows beyond a jump of the Morton order, mostly), or
-// the flagged ones (their lists overflowed).  Nearest tiles by the distance
+// the flagged ones (their lists overflowed).  The smallest is tmin, formed
+// with the bounds: a workgroup reads the bounds of its own rows alone, the
+// others' being written meanwhile.  Nearest tiles by the distance
 // from the point to the box centres as in near_tiles_kernel, then the k-th
 // smallest of the distances to their 2,048 points by bisection on the bit
 // patterns.  A wide bound costs its whole row tile a visit to most of a
@@ -211,7 +222,8 @@ constexpr unsigned kRefineParts = 4;   // workgroups per row tile, each every 4t
 
 __global__ __launch_bounds__(kThreads) void refine_bound_kernel(
     const float *__restrict__ X, const int32_t *__restrict__ perm, const float *__restrict__ box,
-    int64_t n, int64_t nt, int d, int k, const int *__restrict__ flags, float *__restrict__ tau)
+    int64_t n, int64_t nt, int d, int k, const int *__restrict__ flags,
+    const float *__restrict__ tmin, float *__restrict__ tau)
 {
     constexpr int kW = kThreads / kWave;
     constexpr int kPts = kNear * kTileCols / kThreads;
@@ -223,14 +235,12 @@ __global__ __launch_bounds__(kThreads) void refine_bound_kernel(
     const int64_t p0 = (int64_t)(blockIdx.x / kRefineParts) * kTileCols;
     if (wave == 0) {
         const int64_t p = p0 + lane;
-        const int64_t i = p < n ? (int64_t)perm[p] : -1;
-        const float t = (i >= 0) ? tau[i] : INFINITY;
-        float lo = t;
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1)
-            lo = fminf(lo, __shfl_xor(lo, o, kWave));
-        const bool want = i >= 0 && (flags != nullptr ? flags[i] != 0 : t > kWide * lo);
-        const unsigned long long m = __ballot(want && lane % kRefineParts == blockIdx.x % kRefineParts);
+        const int64_t i = (p < n && lane % kRefineParts == blockIdx.x % kRefineParts)
+                              ? (int64_t)perm[p] : -1;
+        const bool want = i >= 0 && (flags != nullptr
+                                         ? flags[i] != 0
+                                         : tau[i] > kWide * tmin[blockIdx.x / kRefineParts]);
+        const unsigned long long m = __ballot(want);
         if (lane == 0)
             todo = m;
     }
@@ -926,7 +936,7 @@ KnnLayout knn_layout(int64_t n, int32_t k)
 
 template <int D>
 void launch_bound(int KT, const float *X, const int32_t *perm, int64_t n, int k,
-                  const int32_t *near, float *tau, hipStream_t s)
+                  const int32_t *near, float *tau, float *tmin, hipStream_t s)
 {
     const int64_t nt = (n + kTileCols - 1) / kTileCols;
     constexpr int kRowTiles = kThreads / kWave;
@@ -934,19 +944,19 @@ void launch_bound(int KT, const float *X, const int32_t *perm, int64_t n, int k,
     switch (KT) {
     case 8:
         hipLaunchKernelGGL((knn_bound_kernel<D, 8>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
-                           near, tau);
+                           near, tau, tmin);
         break;
     case 16:
         hipLaunchKernelGGL((knn_bound_kernel<D, 16>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
-                           near, tau);
+                           near, tau, tmin);
         break;
     case 32:
         hipLaunchKernelGGL((knn_bound_kernel<D, 32>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
-                           near, tau);
+                           near, tau, tmin);
         break;
     default:
         hipLaunchKernelGGL((knn_bound_kernel<D, 64>), grid, dim3(kThreads), 0, s, X, perm, n, nt, k,
-                           near, tau);
+                           near, tau, tmin);
         break;
     }
 }
@@ -1002,23 +1012,28 @@ hipError_t run_knn_graph(const float *X, int64_t n, int d, int k, float sigma,
                        (const int32_t *)perm, n, np, d, 4 * KS, xa, xb, norm2);
     const int64_t ntiles = np / kTileCols;
     float *box = (float *)(w + L.box);
-    // the sort's keys are done with until the edges: the blocks' boxes and
-    // the near tiles take their place (10 bytes a point and at most 256 more,
-    // of 40 or more)
-    float *sub = (float *)(w + L.keyA);
-    int32_t *near = (int32_t *)(w + L.keyA + al(ntiles * kBlocks * 32 * 4));
-    if (L.keyA + al(ntiles * kBlocks * 32 * 4) + (size_t)ntiles * kNear * 4 > L.permA)
+    // the sort's keys are done with until the edges: the blocks' boxes, the
+    // near tiles and the tiles' smallest bounds take their place (at most 11
+    // bytes a point and 772 more; of 40, and the sort's counts, 1,024 or more)
+    size_t at = L.keyA;
+    float *sub = (float *)(w + at);
+    at += (size_t)al(ntiles * kBlocks * 32 * 4);
+    int32_t *near = (int32_t *)(w + at);
+    at += (size_t)al(ntiles * kNear * 4);
+    float *tmin = (float *)(w + at);
+    if (at + (size_t)ntiles * 4 > L.permA)
         return hipErrorInvalidValue;             // not reached
     hipLaunchKernelGGL(tile_box_kernel, dim3((unsigned)((ntiles * 16 + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, s, X, (const int32_t *)perm, n, d, ntiles, box, sub);
     hipLaunchKernelGGL(near_tiles_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, s,
                        (const float *)box, ntiles, d, near);
 
-    // 1. bound, over the Morton neighbours
+    // 1. bound: the near tiles and the Morton neighbours for every row, the
+    // tiles nearest to the row itself where that is wide
     const int KT = k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 ? 32 : 64;
 #define GPIC_BOUND(D)                                                          \
     case D:                                                                    \
-        launch_bound<D>(KT, X, perm, n, k, near, tau, s);                      \
+        launch_bound<D>(KT, X, perm, n, k, near, tau, tmin, s);                \
         break;
     switch (d) {
         GPIC_BOUND(1) GPIC_BOUND(2) GPIC_BOUND(3) GPIC_BOUND(4) GPIC_BOUND(5) GPIC_BOUND(6)
@@ -1031,7 +1046,7 @@ hipError_t run_knn_graph(const float *X, int64_t n, int d, int k, float sigma,
     hipLaunchKernelGGL(refine_bound_kernel, dim3((unsigned)ntiles * kRefineParts),
                        dim3(kThreads), 0, s, X,
                        (const int32_t *)perm, (const float *)box, n, ntiles, d, k,
-                       (const int *)nullptr, tau);
+                       (const int *)nullptr, (const float *)tmin, tau);
     hipLaunchKernelGGL(threshold_kernel, dim3(rows_grid), dim3(kThreads), 0, s, tau,
                        (const double *)nullptr, norm2, maxn, n, d, 4 * KS,
                        (const int *)nullptr, thr);
@@ -1074,7 +1089,7 @@ hipError_t run_knn_graph(const float *X, int64_t n, int d, int k, float sigma,
         hipLaunchKernelGGL(refine_bound_kernel, dim3((unsigned)ntiles * kRefineParts),
                        dim3(kThreads), 0, s, X,
                            (const int32_t *)perm, (const float *)box, n, ntiles, d, k,
-                           (const int *)active, tau);
+                           (const int *)active, (const float *)tmin, tau);
         hipLaunchKernelGGL(threshold_kernel, dim3(rows_grid), dim3(kThreads), 0, s, tau,
                            (const double *)kth, norm2, maxn, n, d, 4 * KS,
                            (const int *)active, thr);

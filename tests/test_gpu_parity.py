@@ -820,6 +820,39 @@ def test_knn_graph_ties(g, orc):
     _check_knn(g, orc, X3, 10, 0.7)         # many duplicate points and ties
 
 
+def _half_duplicates(n, d, rng):
+    """Half of the points on n / 128 places, so that most row tiles hold more
+    than k equal points (whose bound is 0) and others beside them."""
+    X = 3.0 * rng.standard_normal((n, d))
+    P = 3.0 * rng.standard_normal((max(2, n // 128), d))
+    X[: n // 2] = P[rng.integers(0, P.shape[0], n // 2)]
+    return X[rng.permutation(n)].astype(np.float32)
+
+
+def test_knn_bounds_follow_from_the_points(g, monkeypatch):
+    """The rows' bounds (float32 [n], in the scratch behind the operands of
+    80 bytes a padded point twice, the mean's partial sums and the mean) are
+    the same bits whatever the order in which the workgroups of a row tile
+    run."""
+    n, d, k = 40013, 4, 20
+    X = _t(_half_duplicates(n, d, np.random.default_rng(3)))
+    kept, workspace = [], g.workspace
+    monkeypatch.setattr(g, "workspace",
+                        lambda *a, **kw: kept.append(workspace(*a, **kw)) or kept[-1])
+    at = 2 * (((n + 63) // 64 * 64 * 80 + 255) // 256 * 256) + 256 * 16 * 8 + 256
+    bounds = []
+    for _ in range(4):
+        g.gpic_knn_graph(X, k, 1.0)
+        torch.cuda.synchronize()
+        bounds.append(kept.pop()[0][at:at + 4 * n].view(torch.float32).clone())
+    _, place, copies = torch.unique(X, dim=0, return_inverse=True, return_counts=True)
+    zero = bounds[0] == 0.0
+    assert bool((copies[place[zero]] > k).all()) and int(zero.sum()) > n // 3
+    assert bool((bounds[0] >= 0.0).all()) and bool(torch.isfinite(bounds[0]).all())
+    for b in bounds[1:]:
+        assert torch.equal(b, bounds[0])
+
+
 def test_csr_full_pattern_equals_dense(g):
     n = 300
     X = _pts(n, 2, 50)
