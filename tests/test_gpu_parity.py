@@ -829,6 +829,14 @@ def _half_duplicates(n, d, rng):
     return X[rng.permutation(n)].astype(np.float32)
 
 
+@pytest.mark.parametrize("n,d,k", [(2000, 2, 10), (17011, 3, 20), (16449, 8, 64)])
+def test_knn_graph_duplicates(g, orc, n, d, k):
+    """Tiles whose smallest bound is 0: every other row of them is bounded
+    again from the tiles nearest to it."""
+    print(f"knn graph duplicates n={n} d={d} k={k}", flush=True)
+    _check_knn(g, orc, _half_duplicates(n, d, np.random.default_rng(n)), k, 1.0)
+
+
 def test_knn_bounds_follow_from_the_points(g, monkeypatch):
     """The rows' bounds (float32 [n], in the scratch behind the operands of
     80 bytes a padded point twice, the mean's partial sums and the mean) are
