@@ -21,6 +21,8 @@
 #include "kmeans_dev.h"
 #include "kmeans_windows.h"
 
+#include <cstddef>
+
 namespace gpic {
 namespace {
 
@@ -110,13 +112,23 @@ __device__ __forceinline__ void block_scan2(double &x1, double &x2, double *a1, 
 struct KmScalars {
     double mean;
     double distinct;
+    GapStats gaps;                       // in the scratch where the windows may apply
 };
+size_t scalars_bytes(int64_t n, int64_t k)
+{
+    return kmeans_windows_apply(n, k) ? sizeof(KmScalars) : offsetof(KmScalars, gaps);
+}
 
 __global__ __launch_bounds__(1024) void totals_kernel(
     const double *__restrict__ tsum, const double *__restrict__ truns,
-    int64_t nt, int64_t n, KmScalars *__restrict__ sc)
+    int64_t nt, int64_t n, KmScalars *__restrict__ sc, GapStats *__restrict__ gs)
 {
     __shared__ double red[1024 / kWave];
+    if (gs != nullptr && threadIdx.x < kGapClasses) {
+        gs->count[threadIdx.x] = 0ull;
+        gs->sum[threadIdx.x] = 0ull;
+        gs->root[threadIdx.x] = 0ull;
+    }
     double s = 0.0, r = 0.0;
     for (int64_t b = threadIdx.x; b < nt; b += 1024) {
         s += tsum[b];
@@ -973,7 +985,7 @@ inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 unsigned blocks_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
 
 struct KmLayout {
-    size_t keyA, keyB, idxA, idxB, hist, hsum, sv, run, t1, t2, SS, Ea, Eb, opt,
+    size_t keyA, keyB, idxA, idxB, psum, sv, run, t1, t2, SS, Ea, Eb, opt,
         qpart, qnparts, qheads, qbest, qarg, qlen, sc, first, costs, ent, lr, bh, lbase,
         list, total;
 };
@@ -1000,8 +1012,7 @@ KmLayout layout(int64_t n, int32_t k)
     L.keyB = take(n * 8);
     L.idxA = take(n * 4);
     L.idxB = take(n * 4);
-    L.hist = take((size_t)kRadix * nt * 4);
-    L.hsum = take((size_t)tiles(kRadix * nt) * 4);
+    L.psum = take((size_t)(n + 2047) / 2048 * 8);
     L.sv = take(n * 8);
     L.run = take(n * 4);
     L.t1 = take(nt * 8);
@@ -1017,7 +1028,7 @@ KmLayout layout(int64_t n, int32_t k)
     L.qbest = take(cap * fary_f(n) * 8);
     L.qarg = take(cap * fary_f(n) * 4);
     L.qlen = take(4 * 8);
-    L.sc = take(sizeof(KmScalars));
+    L.sc = take(scalars_bytes(n, k));
     L.first = take((size_t)(k + 1) * 8);
     L.costs = take((size_t)k * 8);
     L.ent = take(n * sizeof(RowEntry));
@@ -1048,7 +1059,6 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     char *w = static_cast<char *>(ws);
     uint64_t *keyA = (uint64_t *)(w + L.keyA), *keyB = (uint64_t *)(w + L.keyB);
     int32_t *idxA = (int32_t *)(w + L.idxA), *idxB = (int32_t *)(w + L.idxB);
-    uint32_t *hist = (uint32_t *)(w + L.hist);
     double *sv = (double *)(w + L.sv);
     int32_t *run = (int32_t *)(w + L.run);
     double *t1 = (double *)(w + L.t1), *t2 = (double *)(w + L.t2);
@@ -1067,6 +1077,7 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     int64_t *first = (int64_t *)(w + L.first);
     double *costs = (double *)(w + L.costs);
     const int64_t nt = tiles(n);
+    const bool windows = kmeans_windows_apply(n, k);
 
     if (n <= kTile) {
         int P = 1;
@@ -1088,27 +1099,31 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
     // 2. values, runs, mean, prefix sums
     hipLaunchKernelGGL(decode_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s, keyA,
                        n, sv, run, t1, t2);
-    hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1024), 0, s, t1, t2, nt, n, sc);
+    hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1024), 0, s, t1, t2, nt, n, sc,
+                       windows ? &sc->gaps : (GapStats *)nullptr);
     hipLaunchKernelGGL(tile_moments_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s,
                        sv, n, sc, t1, t2);
     hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(kScanThreads), 0, s, t1, t2, nt);
     hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s, sv,
                        n, sc, t1, t2, SS);
     GPIC_TRY(hipGetLastError());
+    if (windows)
+        GPIC_TRY(launch_gap_stats(sv, SS, n, &sc->gaps, s));
     }
     KmScalars hsc{};
-    GPIC_TRY(hipMemcpyAsync(&hsc, sc, sizeof(hsc), hipMemcpyDeviceToHost, s));
+    GPIC_TRY(hipMemcpyAsync(&hsc, sc, scalars_bytes(n, k), hipMemcpyDeviceToHost, s));
     GPIC_TRY(hipStreamSynchronize(s));
     const int64_t distinct = (int64_t)hsc.distinct;
     const int ke = (int)((int64_t)k < distinct ? k : distinct);
 
     // 3. layers: inside windows around the optimal cuts where these can be
     // found, else every row; both use the scratch from the split table to
-    // the queue's end, and the sort's spare keys (n float64) and histogram
-    // (a KiB per 4,096 values) are free by now
+    // the queue's end, and the sort's spare keys (n float64) are free by now
     int solved = 0;
-    GPIC_TRY(kmeans_windows(sv, run, SS, n, &sc->mean, ke, (double *)keyB, (double *)hist,
-                            w + L.opt, L.qlen - L.opt, first, s, &solved));
+    if (windows)
+        GPIC_TRY(kmeans_windows(sv, run, SS, n, &sc->mean, ke, hsc.gaps, (double *)keyB,
+                                (double *)(w + L.psum), w + L.opt, L.qlen - L.opt, first, s,
+                                &solved));
     if (!solved) {
     hipLaunchKernelGGL(first_layer_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
                        SS, run, n, Ea, Q.qlen);

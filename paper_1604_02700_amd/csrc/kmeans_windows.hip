@@ -9,11 +9,13 @@
 // lower bound B on the cost from it on, and the cost U of the best path
 // that cuts at grid points only.  A grid cell where F + B exceeds U (plus a
 // bound on the float64 rounding) holds no cut of an optimal path; the cells
-// that remain become the next round's windows, cut into cells again, until
-// every position of the windows is a grid point.  The programme over those
-// is the exact one: same candidates around the optimum, same expressions,
-// same order of additions and the leftmost minimum, so it ends with the
-// cuts that the rows of the full programme lead to.
+// that some layer keeps become the next round's windows, cut into cells
+// again, until every position of the windows is a grid point.  The programme
+// over those is the exact one: same candidates around the optimum, same
+// expressions, same order of additions and the leftmost minimum, so its cuts
+// are those that the rows of the full programme lead to, but for ties to the
+// rounding of the costs (n = 2M, k = 12 in clusters 1e-3 wide: one cut a
+// few values away, the total 7e-11 smaller).
 //
 // The bounds.  Let a cell hold s values spanning w (its first to its last).
 // Moving a cut from inside the cell to one of its ends, with the
@@ -30,10 +32,12 @@
 // the cell's left end at the first of them to its right end at the last, at
 // no cost.  Cells take equal shares of the sum of the square roots of the
 // gaps between neighbouring values, which keeps s w even where the values
-// are dense and sparse by turns, and puts a grid point into every wide gap.
-// The terms shrink with the square of the cell, so a few rounds suffice for
-// the embeddings met here; where they do not (values equal to rounding,
-// clusters too many for the grid), the caller runs the full programme.
+// are dense and sparse by turns, and puts a grid point into every wide gap;
+// a gap counts for no more than about a cell, so that a few wide ones do not
+// take the cells of all the values.  The terms shrink with the square of the
+// cell, so a few rounds suffice for the embeddings met here; where they do
+// not (values equal to rounding, clusters too many for the grid), the caller
+// runs the full programme.
 #include "common.h"
 #include "kmeans_dev.h"
 #include "kmeans_windows.h"
@@ -43,39 +47,44 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-// Sizes measured (values of 11 shapes: uniform, normal, heavy tails, tight
-// clusters, integers, the embeddings of the clustering itself).  n = 2M, k =
-// 50: 19.1 -> 4.2 ms for the embedding, 15-20 -> 1.4-4.4 ms for the others
-// but one (half as many clusters as k: not solved, 15.5 -> 17.1 ms); n =
-// 300,000, k = 24: 3.8 -> 1.0-2.1 ms; n = 20,000, k = 10: 0.75 -> 0.56 ms.
-// Cells of a later window: 512 instead of 1,024 a layer fails for some of
-// them; rows of 4 x instead of 8 x fail for two at k = 50; a first round of
-// 1,024 cells costs 0.1-0.3 ms more, of 256 leaves wider windows.  Below
-// 8,192 values the full programme is two or three levels a layer and the
-// scratch holds few cells (n = 5,000, k = 24: 0.7-1.9 ms against 1.3).
-// With few clusters the full programme is short as well, three launches a
-// level for each layer but the last, and below 2^18 values it has three
-// levels: n = 10,000, k = 3, 5, 7, 10: 0.40, 0.50, 0.61, 0.76 ms against 0.47,
-// 0.50, 0.56, 0.64; n = 50,000, k = 3, 6, 8: 0.43, 0.62, 0.72 against 0.48,
-// 0.60, 0.70.  From 2^18 values it has six or more: n = 270,000, k = 3: 0.72
-// against 0.68; n = 2M, k = 3: 1.35 against 1.03.
-constexpr int64_t kFromN = 8192;
-constexpr int64_t kLargeN = (int64_t)1 << 18;
-constexpr int kFewSmall = 7;
+// Where the windows are tried, measured against the full programme in the
+// same run: 13 shapes of values (uniform, normal, heavy tails, integers, as
+// many and fewer clusters than k from 1e-9 to 1e-3 wide and of widely
+// different widths), 3 to 5 draws each.  Below 8,192 values the full
+// programme is two or three levels a layer and the scratch holds few cells.
+// Up to 2^17 it has three levels, about 75 us a layer, and with few clusters
+// nothing is gained (k = 7: 1.1 times as fast at n = 12,000, level at
+// 60,000, slower for half of the shapes); k = 10 at n = 8,192, 20,000,
+// 40,000, 120,000: 1.25, 1.23, 1.17, 1.27 (geometric means); k = 24 at 20,000
+// and 60,000: 1.38, 1.41.  n = 140,000, k = 7, 30: 1.19, 1.78; n = 270,000, k = 3,
+// 7, 24: 1.05, 1.53, 2.35; n = 600,000, k = 5, 40: 1.47, 2.9; n = 2M, k = 3, 5,
+// 50: 1.29, 1.75, 4.2 (19.2 ms without).  Of the 3,302 measured under these
+// rules 18 took more than 1.05 times as long as the full programme, the worst
+// 1.3 times (fewer clusters than k, of widths 1e-2 to 1e-10, the cost near the
+// rounding), n = 30,000 and 40,000 with k = 10 up to 1.09.
+// Cells: a first round of 1,024 costs 0.1-0.3 ms more, of 256 leaves wider
+// windows; rows of 4 x kMaxPer instead of 8 x lose from k = 50 on.
+constexpr int64_t kFromN = 8192, kLargeN = (int64_t)1 << 17, kHugeN = (int64_t)1 << 18;
+constexpr int kFewSmall = 10, kFewLarge = 7, kFewHuge = 3;   // clusters below, from kLargeN, kHugeN
+// Costs of spare cuts up to this many times the bound on the rounding leave
+// windows too wide (clusters of 1e-9 to 1e-12 of the range, fewer than k: a
+// quarter of the full programme's time lost in two rounds that keep everything;
+// with clusters of 1e-4 they are 2e5 times and more).
+constexpr double kRoundingCost = 1e5;
 constexpr int kFirst = 512;              // cells of the first round
 constexpr int kMaxPer = 1024;            // cells per layer of a window later
-constexpr int kMaxMerged = 8;            // a window of several layers: up to this many times as many
+constexpr int kMaxMerged = 8;            // a layer's range: up to this many times as many
 constexpr int kMaxClusters = 512;
 constexpr int kMaxRounds = 5;
 
 // What a round leaves for the host.
 struct RoundCtl {
-    int32_t nseg;                        // merged windows
+    int32_t nseg;                        // windows
     int32_t total;                       // grid points of the next round
-    int32_t rows;                        // most grid points of a layer's window
+    int32_t rows;                        // most grid points of a layer's range
     int32_t exact;                       // every position of the windows is a grid point
-    int32_t fail;                        // a layer lost every cell
-    int64_t span;                        // positions in all windows
+    int32_t fail;                        // a layer lost every cell, or no room for smaller ones
+    int32_t span;                        // positions in all windows
     double thr;                          // no path above this cost is optimal
 };
 
@@ -87,7 +96,8 @@ struct View {
     const int32_t *run;                  // 1 where a run of equal values starts
     const double2 *SS;                   // prefix sums (S1, S2)
     int64_t n;
-    int32_t ke, stride, per;
+    int32_t ke, stride, per, points;     // points: room for grid points
+    double cap;                          // most that one gap adds to phi
     int32_t *pos;                        // grid point -> position
     double2 *S;                          // SS at the position
     const double *mean;                  // of the values
@@ -101,10 +111,11 @@ struct View {
     int32_t *arg;
     int32_t *cellseg;                    // 1: first grid point of its window, 2: last
     int32_t *qmin, *rmax;                // furthest grid point that one segment can reach
-    int32_t *lo, *hi;                    // kept positions per layer
-    int32_t *seg;                        // window of the layer
+    int32_t *keepp, *keepc;              // grid points, cells to their right, that some layer keeps
+    int32_t *lo, *hi;                    // first and last kept position of a layer
     int32_t *wa, *wb;                    // its first and last grid point
     int32_t *segP, *segQ, *base;         // positions and first grid point of a window
+    int32_t *kpre, *lpre, *mpre;         // of the windows before: kept cells, positions, windows with cells
     RoundCtl *ctl;
 };
 
@@ -132,16 +143,53 @@ __device__ __forceinline__ int32_t snap(const View &V, int32_t p)
     return a;
 }
 
-// phi[i] = sum over j <= i of sqrt(x_j - x_{j-1}): tile sums, their scan by
+// phi[i] = sum over j <= i of sqrt(x_j - x_{j-1}), at most cap each: tile sums, their scan by
 // one workgroup, the tiles again from their offsets.  Any non-decreasing
 // phi gives valid cells; its rounding does not matter.
 __device__ __forceinline__ double gap_root(const View &V, int64_t i)
 {
-    return (i > 0 && i < V.n) ? sqrt(fmax(V.sv[i] - V.sv[i - 1], 0.0)) : 0.0;
+    return (i > 0 && i < V.n) ? fmin(sqrt(fmax(V.sv[i] - V.sv[i - 1], 0.0)), V.cap) : 0.0;
 }
 
 constexpr int kItems = 8;
 constexpr int kTile = kThreads * kItems;
+
+// A workgroup's gaps by class in LDS, then an atomic per class that it met.
+__global__ __launch_bounds__(kThreads) void gap_stats_kernel(const double *__restrict__ sv,
+                                                             const double2 *__restrict__ SS,
+                                                             int64_t n, GapStats *__restrict__ gs)
+{
+    __shared__ unsigned long long sum[kGapClasses], root[kGapClasses];
+    __shared__ unsigned int count[kGapClasses];
+    if (threadIdx.x < kGapClasses) {
+        sum[threadIdx.x] = 0ull;
+        root[threadIdx.x] = 0ull;
+        count[threadIdx.x] = 0u;
+    }
+    __syncthreads();
+    const double R = sv[n - 1] - sv[0];
+    for (int64_t i = 1 + (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kThreads) {
+        const double q = (sv[i] - sv[i - 1]) / R;
+        if (!(q > 0.0 && q <= 1.0))
+            continue;                                // equal values, or no finite range
+        const int e = -ilogb(q);
+        const int b = e < kGapClasses ? e : kGapClasses - 1;
+        atomicAdd(&count[b], 1u);
+        atomicAdd(&sum[b], (unsigned long long)(q * 0x1p60));
+        atomicAdd(&root[b], (unsigned long long)(sqrt(q) * 0x1p40));
+    }
+    __syncthreads();
+    if (threadIdx.x < kGapClasses && count[threadIdx.x] != 0u) {
+        atomicAdd(&gs->count[threadIdx.x], (unsigned long long)count[threadIdx.x]);
+        atomicAdd(&gs->sum[threadIdx.x], sum[threadIdx.x]);
+        atomicAdd(&gs->root[threadIdx.x], root[threadIdx.x]);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        gs->range = R;
+        gs->s2 = SS[n].y;
+    }
+}
 
 __global__ __launch_bounds__(kThreads) void phi_sums_kernel(View V)
 {
@@ -190,7 +238,6 @@ __global__ __launch_bounds__(1024) void first_window_kernel(View V, int64_t tile
         o += x;
     }
     for (int c = threadIdx.x; c < V.ke; c += 1024) {
-        V.seg[c] = 0;
         V.lo[c] = 0;
         V.hi[c] = (int32_t)(V.n - 1);
     }
@@ -273,9 +320,7 @@ __global__ __launch_bounds__(kThreads) void grid_kernel(View V)
     const int32_t i = (int32_t)(blockIdx.x * kThreads + threadIdx.x);
     const int32_t total = V.ctl->total;
     if (i >= 1 && i < V.ke) {
-        const int z = V.seg[i];
-        const int32_t a = V.base[z], b = V.base[z + 1] - 1;
-        int32_t x = a, y = b;            // last with pos <= lo
+        int32_t x = 0, y = total - 1;    // last with pos <= lo
         while (x < y) {
             const int32_t m = x + (y - x + 1) / 2;
             if (V.pos[m] <= V.lo[i])
@@ -284,7 +329,7 @@ __global__ __launch_bounds__(kThreads) void grid_kernel(View V)
                 y = m - 1;
         }
         V.wa[i] = x;
-        y = b;                           // first with pos >= hi
+        y = total - 1;                   // first with pos >= hi
         while (x < y) {
             const int32_t m = x + (y - x) / 2;
             if (V.pos[m] < V.hi[i])
@@ -296,6 +341,8 @@ __global__ __launch_bounds__(kThreads) void grid_kernel(View V)
     }
     if (i >= total)
         return;
+    V.keepp[i] = 0;
+    V.keepc[i] = 0;
     const double thr = V.ctl->thr;
     auto over = [&](int32_t q, int32_t r) {      // no segment from near q to near r
         if (q + 1 >= r - 1)
@@ -355,11 +402,15 @@ __global__ __launch_bounds__(kThreads) void grid_kernel(View V)
 // Distance between x, an end of a cell, and the mean of the (centred) values
 // between the positions in a and b: above, the mean less x, else x less the
 // mean.  The callers pass the neighbouring grid points that give the extreme
-// mean, and add 2^-18 of the values' range, more than the approximate
-// reciprocal is off.
+// mean, and add kMeanSlack of the values' range: the reciprocal is good to
+// 2^-18 and better, which the Newton step squares.
+constexpr double kMeanSlack = 0x1p-35;
 __device__ __forceinline__ double mean_dist(double2 a, double2 b, double x, bool above)
 {
-    const double q = (b.x - a.x) * __builtin_amdgcn_rcp(b.y - a.y);
+    const double m = b.y - a.y;
+    double r = __builtin_amdgcn_rcp(m);
+    r = fma(fma(-m, r, 1.0), r, r);
+    const double q = (b.x - a.x) * r;
     return above ? q - x : x - q;
 }
 
@@ -377,7 +428,7 @@ __device__ __forceinline__ double wave_min(double x)
 // layer ke - t), a wave per grid point of the layer's window.  EXACT: every
 // position is a grid point, the forward programme alone, with its argmins.
 // A layer is 513 x 513 evaluations in the first round and mostly fewer
-// later, except while windows are merged (up to 8,193 rows: 35 us); the
+// later, except while its range is wide (up to 8,193 rows: 35 us); the
 // launches, about 5 us each, are most of the rest.
 template <bool EXACT>
 __global__ __launch_bounds__(kThreads) void layer_kernel(View V, int t)
@@ -392,7 +443,7 @@ __global__ __launch_bounds__(kThreads) void layer_kernel(View V, int t)
     const int32_t p = V.pos[r];
     const double2 Sr = V.S[r];
     // of a distance: rounding of the values (eta) and of the means
-    const double slack = EXACT ? 0.0 : eta_of(V) + 0x1p-18 * (V.sv[V.n - 1] - V.sv[0]);
+    const double slack = EXACT ? 0.0 : eta_of(V) + kMeanSlack * (V.sv[V.n - 1] - V.sv[0]);
     const int64_t row = (int64_t)c * V.stride + (r - a);
     if (!back) {
         double f = INFINITY, u = INFINITY, vf = INFINITY;
@@ -492,8 +543,14 @@ __global__ __launch_bounds__(kThreads) void layer_kernel(View V, int t)
     }
 }
 
-// A workgroup per layer: the positions of its window that a path of cost at
-// most the best known one can cut at.
+// (several layers' workgroups mark one cell)
+__device__ __forceinline__ void mark(int32_t *p)
+{
+    __hip_atomic_store(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A workgroup per layer: the grid points and cells of its range that a path
+// of cost at most the best known one can cut at.
 __global__ __launch_bounds__(kThreads) void prune_kernel(View V)
 {
     __shared__ double red[kWaves];
@@ -530,6 +587,7 @@ __global__ __launch_bounds__(kThreads) void prune_kernel(View V)
         if (T <= thr) {
             lo = min(lo, V.pos[i]);
             hi = max(hi, V.pos[i]);
+            mark(V.keepp + i);
         }
         if (i < b && V.pen[i] >= 0.0) {
             const double vf = V.Vf[e], vb = V.Vb[e];
@@ -538,6 +596,7 @@ __global__ __launch_bounds__(kThreads) void prune_kernel(View V)
             if (m <= thr) {
                 lo = min(lo, V.pos[i]);
                 hi = max(hi, V.pos[i + 1]);
+                mark(V.keepc + i);
             }
         }
     }
@@ -561,69 +620,201 @@ __global__ __launch_bounds__(kThreads) void prune_kernel(View V)
     }
 }
 
-// The next round's windows: the layers' kept ranges, made monotone, merged
-// where they overlap, each cut into `per` cells for every layer that has its
-// range there, up to kMaxMerged times that (as many as the rows hold).
-__global__ __launch_bounds__(kThreads) void windows_kernel(View V)
+// Inclusive scan over the workgroup of one whole number per thread.
+template <int NT>
+__device__ __forceinline__ int32_t block_scan_incl(int32_t x, int32_t *a)
 {
+    const int t = threadIdx.x;
+    __syncthreads();
+    a[t] = x;
+    __syncthreads();
+    for (int off = 1; off < NT; off <<= 1) {
+        const int32_t o = t >= off ? a[t - off] : 0;
+        __syncthreads();
+        x += o;
+        a[t] = x;
+        __syncthreads();
+    }
+    return x;
+}
+
+// The next round's windows: the runs of neighbouring cells that some layer
+// keeps (a kept point beside no kept cell is one by itself), each cut into
+// `split` cells for every one it had and `extra` more, as many as the grid
+// and the rows hold, half of the room for either, or into every position
+// where there is room for all of them.  A layer's range is
+// that of the cells it keeps, made monotone over the layers; what lies in it
+// between windows is left out, so that a few far apart ways to place the
+// cuts (k above the number of clusters) do not keep all that lies between.
+constexpr int kWinThreads = 1024;
+static_assert(kMaxClusters <= kWinThreads, "a thread per layer");
+
+__global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
+{
+    __shared__ int32_t a[kWinThreads];
     __shared__ int32_t lo[kMaxClusters], hi[kMaxClusters];
-    for (int c = 1 + (int)threadIdx.x; c < V.ke; c += kThreads) {
-        lo[c] = V.lo[c];
-        hi[c] = V.hi[c];
+    __shared__ int32_t split, extra, rows, fail, all, exact;
+    const int t = threadIdx.x;
+    const int c = t;                             // the thread's layer, if any
+    const bool layer = c >= 1 && c < V.ke;
+    if (t == 0) {
+        split = extra = INT32_MAX;
+        rows = fail = 0;
+        all = exact = 1;
     }
     __syncthreads();
-    if (threadIdx.x != 0)
+    if (layer) {
+        lo[c] = V.lo[c];
+        hi[c] = V.hi[c];
+        if (lo[c] > hi[c])
+            atomicOr(&fail, 1);
+    }
+    __syncthreads();
+    if (fail != 0) {                             // uniform
+        if (t == 0)
+            V.ctl->fail = 1;
         return;
-    // squares that overflow leave no bound that means anything: every row is
-    // computed instead
-    int fail = !(V.SS[V.n].y < INFINITY);
-    for (int c = 1; c < V.ke; ++c)
-        fail |= lo[c] > hi[c];
-    for (int c = V.ke - 2; c >= 1; --c)
-        lo[c] = min(lo[c], lo[c + 1]);
-    for (int c = 2; c < V.ke; ++c)
-        hi[c] = max(hi[c], hi[c - 1]);
-    int z = -1, total = 0, rows = 0, exact = 1, layers = 0;
-    int32_t P = 0, Q = -1;
-    int64_t span = 0;
-    auto close = [&]() {
-        V.segP[z] = P;
-        V.segQ[z] = Q;
-        V.base[z] = total;
-        const int32_t len = Q - P;
-        const int64_t most = min((int64_t)V.per * layers, (int64_t)V.stride - 1);
-        const int32_t cells = (int32_t)min((int64_t)len, most);
-        total += cells + 1;
-        rows = max(rows, cells + 1);
-        exact &= cells == len;
-        span += len + 1;
-        layers = 0;
-    };
-    for (int c = 1; c < V.ke && !fail; ++c) {
-        if (z < 0 || lo[c] > Q) {
-            if (z >= 0)
-                close();
-            ++z;
-            P = lo[c];
-            Q = hi[c];
-        } else {
-            Q = max(Q, hi[c]);
+    }
+    for (int off = 1; off < V.ke; off <<= 1) {
+        const int32_t l = layer && c + off < V.ke ? lo[c + off] : INT32_MAX;
+        const int32_t h = layer && c - off >= 1 ? hi[c - off] : -1;
+        __syncthreads();
+        if (layer) {
+            lo[c] = min(lo[c], l);
+            hi[c] = max(hi[c], h);
         }
-        ++layers;
-        V.seg[c] = z;
+        __syncthreads();
+    }
+    // windows, kept cells and their positions before a thread's grid points
+    const int32_t n = V.ctl->total;
+    const int32_t per = (n + kWinThreads - 1) / kWinThreads;
+    const int32_t i0 = t * per, i1 = min(i0 + per, n);
+    int32_t s = 0, m = 0, k = 0, l = 0;
+    bool left = i0 > 0 && i0 < i1 && V.keepc[i0 - 1] != 0;
+    for (int32_t i = i0; i < i1; ++i) {
+        const bool cell = V.keepc[i] != 0;
+        s += (cell || V.keepp[i] != 0) && !left;
+        m += cell && !left;
+        if (cell) {
+            ++k;
+            l += V.pos[i + 1] - V.pos[i];
+        }
+        left = cell;
+    }
+    int32_t ws = block_scan_incl<kWinThreads>(s, a);
+    const int32_t nseg = a[kWinThreads - 1];
+    int32_t wm = block_scan_incl<kWinThreads>(m, a);
+    const int32_t wide = a[kWinThreads - 1];
+    int32_t wk = block_scan_incl<kWinThreads>(k, a);
+    const int32_t cells = a[kWinThreads - 1];
+    int32_t wl = block_scan_incl<kWinThreads>(l, a);
+    const int32_t span = a[kWinThreads - 1] + nseg;
+    ws -= s;
+    wm -= m;
+    wk -= k;
+    wl -= l;
+    left = i0 > 0 && i0 < i1 && V.keepc[i0 - 1] != 0;
+    for (int32_t i = i0; i < i1; ++i) {
+        const bool cell = V.keepc[i] != 0;
+        const bool in = cell || V.keepp[i] != 0 || left;
+        if (in && !left) {
+            V.segP[ws] = V.pos[i];
+            V.kpre[ws] = wk;
+            V.lpre[ws] = wl + ws;
+            V.mpre[ws] = wm;
+            ++ws;
+            wm += cell;
+        }
+        if (in && !cell)
+            V.segQ[ws - 1] = V.pos[i];
+        if (cell) {
+            ++wk;
+            wl += V.pos[i + 1] - V.pos[i];
+        }
+        left = cell;
+    }
+    if (t == 0) {
+        V.kpre[nseg] = cells;
+        V.lpre[nseg] = span;
+        V.mpre[nseg] = wide;
+    }
+    __syncthreads();
+    // the layer's windows, and how far its rows let the cells be split
+    int32_t zl = 0, zh = 0;
+    if (layer) {
+        auto at = [&](int32_t p) {               // last window that starts at or before p
+            int32_t x = 0, y = nseg - 1;
+            while (x < y) {
+                const int32_t m = (x + y + 1) / 2;
+                if (V.segP[m] <= p)
+                    x = m;
+                else
+                    y = m - 1;
+            }
+            return x;
+        };
+        zl = at(lo[c]);
+        zh = at(hi[c]);
+        const int32_t half = max(V.stride - (zh - zl + 1), 0) / 2;
+        const int32_t kc = V.kpre[zh + 1] - V.kpre[zl], mc = V.mpre[zh + 1] - V.mpre[zl];
+        if (V.lpre[zh + 1] - V.lpre[zl] > V.stride)
+            atomicAnd(&all, 0);
+        if (kc > 0) {
+            atomicMin(&split, half / kc);
+            atomicMin(&extra, half / mc);
+        }
+    }
+    if (t == 0) {
+        if (span > V.points)
+            atomicAnd(&all, 0);
+        const int32_t half = max(V.points - nseg, 0) / 2;
+        if (cells > 0) {
+            atomicMin(&split, half / cells);
+            atomicMin(&extra, half / wide);
+        }
+    }
+    __syncthreads();
+    const int64_t f = split, g = extra;
+    const bool every = all != 0;
+    // the windows' first grid points
+    const int32_t wper = (nseg + kWinThreads - 1) / kWinThreads;
+    const int32_t z0 = t * wper, z1 = min(z0 + wper, nseg);
+    auto points = [&](int32_t z) {
+        const int32_t len = V.segQ[z] - V.segP[z];
+        const int64_t k = V.kpre[z + 1] - V.kpre[z];
+        const int64_t most = k > 0 ? f * k + g : 0;
+        return (every ? len : (int32_t)min((int64_t)len, most)) + 1;
+    };
+    int32_t b = 0;
+    for (int32_t z = z0; z < z1; ++z) {
+        const int32_t x = points(z);
+        if (x != V.segQ[z] - V.segP[z] + 1)
+            atomicAnd(&exact, 0);
+        b += x;
+    }
+    int32_t o = block_scan_incl<kWinThreads>(b, a) - b;
+    const int32_t total = a[kWinThreads - 1];
+    for (int32_t z = z0; z < z1; ++z) {
+        V.base[z] = o;
+        o += points(z);
+    }
+    if (t == 0)
+        V.base[nseg] = total;
+    __syncthreads();
+    if (layer) {
         V.lo[c] = lo[c];
         V.hi[c] = hi[c];
+        atomicMax(&rows, V.base[zh + 1] - V.base[zl]);
     }
-    if (!fail) {
-        close();
-        V.base[z + 1] = total;
+    __syncthreads();
+    if (t == 0) {
+        V.ctl->nseg = nseg;
+        V.ctl->total = total;
+        V.ctl->rows = rows;
+        V.ctl->exact = exact;
+        V.ctl->fail = !every && f + g < 2;
+        V.ctl->span = span;
     }
-    V.ctl->nseg = z + 1;
-    V.ctl->total = total;
-    V.ctl->rows = rows;
-    V.ctl->exact = exact;
-    V.ctl->fail = fail;
-    V.ctl->span = span;
 }
 
 // Row n - 1 of the last layer and the way back through the argmins.
@@ -684,6 +875,7 @@ size_t place(char *ws, int64_t n, int32_t ke, int32_t per, int32_t merged, View 
     const int64_t later = (int64_t)(ke - 1) * (per + 1);
     const size_t pts = (size_t)(later < n + ke ? later : n + ke);
     const size_t rows = (size_t)ke * V->stride;
+    V->points = (int32_t)pts;
     V->ctl = (RoundCtl *)take(sizeof(RoundCtl));
     V->pos = (int32_t *)take(pts * 4);
     V->S = (double2 *)take(pts * 16);
@@ -705,27 +897,118 @@ size_t place(char *ws, int64_t n, int32_t ke, int32_t per, int32_t merged, View 
     V->hi = (int32_t *)take((size_t)ke * 4);
     V->qmin = (int32_t *)take(pts * 4);
     V->rmax = (int32_t *)take(pts * 4);
-    V->seg = (int32_t *)take((size_t)ke * 4);
+    V->keepp = (int32_t *)take(pts * 4);
+    V->keepc = (int32_t *)take(pts * 4);
     V->wa = (int32_t *)take((size_t)ke * 4);
     V->wb = (int32_t *)take((size_t)ke * 4);
-    V->segP = (int32_t *)take((size_t)ke * 4);
-    V->segQ = (int32_t *)take((size_t)ke * 4);
-    V->base = (int32_t *)take((size_t)(ke + 1) * 4);
+    V->segP = (int32_t *)take(pts * 4);
+    V->segQ = (int32_t *)take(pts * 4);
+    V->base = (int32_t *)take((pts + 1) * 4);
+    V->kpre = (int32_t *)take((pts + 1) * 4);
+    V->lpre = (int32_t *)take((pts + 1) * 4);
+    V->mpre = (int32_t *)take((pts + 1) * 4);
     return o;
 }
 
 } // namespace
 
+bool kmeans_windows_apply(int64_t n, int64_t k)
+{
+    return n >= kFromN && k >= (n < kLargeN ? kFewSmall : n < kHugeN ? kFewLarge : kFewHuge);
+}
+
+hipError_t launch_gap_stats(const double *sv, const double2 *SS, int64_t n, GapStats *gs,
+                            hipStream_t s)
+{
+    const int64_t want = (n + kTile - 1) / kTile;
+    hipLaunchKernelGGL(gap_stats_kernel, dim3((unsigned)(want < 256 ? want : 256)),
+                       dim3(kThreads), 0, s, sv, SS, n, gs);
+    return hipGetLastError();
+}
+
+namespace {
+
+// Whether the windows can be expected to shrink, from the gaps alone.  At a
+// scale, the gaps above it split the values into groups, of mean width w (the
+// sum of the others over their number).
+//   * Where the values form fewer groups than ke, the cuts to spare are
+//     decided by costs of about n w^2 / 64 (a deviation of w / 8).  Where that
+//     is near the bound on the rounding, no bound excludes anything, unless the
+//     next gaps give the ke groups and leave far less inside them.
+//   * Up to kLargeN values, where they form well separated groups (w below a
+//     quarter of every gap between them) and these are two thirds of ke or
+//     fewer: many ways to hand out the spare cuts cost about the same, and the
+//     scratch is small for a grid that tells them apart.
+// Only the time depends on it.
+bool worth_it(const GapStats &gs, int64_t n, int32_t ke)
+{
+    const double pad = (0x1p-44 + ke * 0x1p-50) * gs.s2;
+    double inside = 0.0;
+    for (int b = 0; b < kGapClasses; ++b)
+        inside += (double)gs.sum[b];
+    inside *= 0x1p-60;
+    double finest = inside, groups = 1.0, separate = 1.0, last = -1.0;
+    for (int b = 0; b < kGapClasses && groups <= ke; ++b) {
+        // the groups at the gaps of the classes below b
+        if (groups < ke) {
+            finest = inside / groups;
+            if (groups > 1.0 && finest < 0.25 * exp2(1.0 - b))
+                separate = groups;
+        } else if (last < 0.0) {
+            last = inside / groups;
+        }
+        groups += (double)gs.count[b];
+        inside -= (double)gs.sum[b] * 0x1p-60;
+    }
+    if (last >= 0.0 && last < 0.0625 * finest)
+        return true;
+    const double w = finest * gs.range;
+    if ((double)n * w * w * 0x1p-6 <= kRoundingCost * pad)
+        return false;
+    return !(n < kLargeN && separate > 1.0 && 3.0 * separate <= 2.0 * ke);
+}
+
+// The most that one gap adds to phi: a wide gap needs one grid point, and
+// without a bound a few of them take the cells of all the values.  The
+// smallest class limit that is still a cell's share where every wider gap
+// counts as much as it.
+double root_cap(const GapStats &gs, int32_t cells)
+{
+    double rest = 0.0, wide = 0.0, cap = INFINITY;
+    for (int b = 0; b < kGapClasses; ++b)
+        rest += (double)gs.root[b] * 0x1p-40;
+    for (int b = 0; b < kGapClasses; ++b) {
+        const double c = exp2(-0.5 * b);             // the largest root of class b
+        if (c * cells < rest + wide * c)
+            break;
+        cap = c;
+        wide += (double)gs.count[b];
+        rest -= (double)gs.root[b] * 0x1p-40;
+    }
+    return cap * sqrt(gs.range);
+}
+
+} // namespace
+
 hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *SS, int64_t n,
-                          const double *mean, int32_t ke, double *phi, double *psum, void *ws,
-                          size_t ws_bytes, int64_t *first, hipStream_t s, int *solved)
+                          const double *mean, int32_t ke, const GapStats &gs, double *phi,
+                          double *psum, void *ws, size_t ws_bytes, int64_t *first,
+                          hipStream_t s, int *solved)
 {
     *solved = 0;
-    if (ke < (n < kLargeN ? kFewSmall : 3) || ke > kMaxClusters || n < kFromN)
+    if (!kmeans_windows_apply(n, ke) || ke > kMaxClusters)
         return hipSuccess;
-    // cells of the first round, and rows for merged windows: as many as are
-    // useful and the scratch holds; with few per cluster the windows would
-    // not shrink (a window is about sqrt(4 ke) / (cells per cluster) of one)
+    // squares that overflow leave no bound that means anything: every row is
+    // computed
+    if (!(gs.s2 < INFINITY) || !worth_it(gs, n, ke))
+        return hipSuccess;
+    // cells of the first round, and rows of a layer: as many as are useful and
+    // the scratch holds; with few per cluster the windows do not shrink (one is
+    // about sqrt(4 ke) / (cells per cluster) of it).  10 ke^1.5: n = 20,000, k =
+    // 24 (10.3) 1.38 times as fast, 12,000 and 24 (7.0) 1.29 with a tenth of the
+    // draws at 0.7, 40,000 and 48 (5.4) 1.15 with a third; 1,050,000 and 70
+    // (14) 3.8, 600,000 and 100 (8.2) 2.9 with one in thirteen at 0.75, 1,050,000 and
+    // 120 (6.2) 2.1 with two in five at 0.8
     View V{};
     int32_t per = (int32_t)(n / 4 < kMaxPer ? n / 4 : kMaxPer), merged = kMaxMerged;
     while (per >= 32 && place(nullptr, n, ke, per, merged, &V) > ws_bytes) {
@@ -735,7 +1018,7 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
             per -= (per + 15) / 16;
     }
     const double cells = (double)per * (merged < ke - 1 ? merged : ke - 1);
-    if (per < 32 || per < 2 * ke || (cells < (double)n && cells < 4.0 * ke * sqrt((double)ke)))
+    if (per < 32 || per < 2 * ke || (cells < (double)n && cells < 10.0 * ke * sqrt((double)ke)))
         return hipSuccess;
     place(static_cast<char *>(ws), n, ke, per, merged, &V);
     V.sv = sv;
@@ -747,6 +1030,7 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
     V.psum = psum;
     const int64_t tiles = (n + kTile - 1) / kTile;
     const int32_t first_cells = per < kFirst ? per : kFirst;
+    V.cap = root_cap(gs, first_cells);
     hipLaunchKernelGGL(phi_sums_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, s, V);
     hipLaunchKernelGGL(first_window_kernel, dim3(1), dim3(1024), 0, s, V, tiles, first_cells);
     hipLaunchKernelGGL(phi_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, s, V);
@@ -761,7 +1045,7 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
         for (int t = 1; t < ke; ++t)
             hipLaunchKernelGGL(layer_kernel<false>, dim3(wg, 2), dim3(kThreads), 0, s, V, t);
         hipLaunchKernelGGL(prune_kernel, dim3((unsigned)(ke - 1)), dim3(kThreads), 0, s, V);
-        hipLaunchKernelGGL(windows_kernel, dim3(1), dim3(kThreads), 0, s, V);
+        hipLaunchKernelGGL(windows_kernel, dim3(1), dim3(kWinThreads), 0, s, V);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -771,8 +1055,13 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
             return e;
         if (h.fail)
             return hipSuccess;
+        // neither the windows nor their cells get smaller (the first grid may
+        // be too coarse to exclude anything yet)
+        const bool stuck = round > 0 && h.span > 0.75 * span &&
+                           (double)h.span / h.total > 0.75 * span / total;
         total = h.total;
         rows = h.rows;
+        span = h.span;
         if (h.exact) {
             // every position of the windows is a grid point: the programme itself
             const unsigned ge = (unsigned)(((total > ke ? total : ke) + kThreads - 1) / kThreads);
@@ -785,11 +1074,8 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
             *solved = 1;
             return hipGetLastError();
         }
-        // the windows no longer shrink (the first grid may be too coarse to
-        // exclude anything yet)
-        if (round > 0 && h.span > span - span / 8)
+        if (stuck)
             return hipSuccess;
-        span = h.span;
     }
     return hipSuccess;
 }

@@ -465,6 +465,60 @@ def test_kmeans1d_windows(g, orc, n, k, shape):
     check_kmeans(v, out, orc.kmeans1d(v, k, "dc"))
 
 
+def _kmeans_solver(g, monkeypatch, v, k):
+    """gpic_kmeans1d and which solver took it: the full programme lays its
+    lists of rows out at the end of the scratch (16 bytes a value), the
+    windows leave that part as it was."""
+    kept, workspace = [], g.workspace
+
+    def filled(*a, **kw):
+        buf, nbytes = workspace(*a, **kw)
+        buf.fill_(0xA5)
+        kept.append(buf)
+        return buf, nbytes
+
+    with monkeypatch.context() as m:
+        m.setattr(g, "workspace", filled)
+        out = g.gpic_kmeans1d(_t(v), k)
+    torch.cuda.synchronize()
+    return out, "windows" if bool((kept[0][-16 * v.size:] == 0xA5).all()) else "rows"
+
+
+def _clusters(n, m, width, rng):
+    return rng.random(m)[rng.integers(m, size=n)] + width * rng.standard_normal(n)
+
+
+@pytest.mark.parametrize("n,k,shape,solver", [
+    (8191, 10, "normal", "rows"), (8192, 9, "normal", "rows"), (8192, 10, "normal", "windows"),
+    (8192, 24, "normal", "rows"), (20011, 10, "normal", "windows"),
+    (20011, 16, "tail", "windows"), (60000, 24, "tight", "windows"),
+    (60000, 24, "fewer", "rows"), (131071, 9, "normal", "rows"),
+    (131072, 7, "normal", "windows"), (131072, 24, "fewer", "windows"),
+    (262143, 6, "tail", "rows"), (262144, 3, "tail", "windows"),
+    (262144, 50, "fewer", "windows"), (300007, 12, "rounding", "rows"),
+    (300007, 40, "tight", "windows"), (400000, 60, "fewer", "windows"),
+    (300007, 512, "normal", "rows"), (600001, 80, "uniform", "windows")])
+def test_kmeans1d_solver(g, orc, monkeypatch, n, k, shape, solver):
+    """Which values the windows solve and which take the full programme, on
+    both sides of the rules (sizes, clusters, scratch for the cells, fewer
+    clusters than k, costs near the rounding), and the optimum either way."""
+    rng = np.random.default_rng(n + k)
+    v = {"normal": lambda: rng.standard_normal(n),
+         "uniform": lambda: rng.random(n),
+         "tail": lambda: rng.exponential(1.0, n) ** 3,
+         "tight": lambda: _clusters(n, k, 1e-9, rng),
+         "fewer": lambda: _clusters(n, k // 2, 1e-4, rng),
+         "rounding": lambda: _clusters(n, k // 2, 1e-10, rng)}[shape]()
+    print(f"kmeans solver n={n} k={k} {shape}", flush=True)
+    out, took = _kmeans_solver(g, monkeypatch, v, k)
+    assert took == solver
+    if shape != "rounding":                  # the costs differ by their rounding alone
+        check_kmeans(v, out, orc.kmeans1d(v, k, "dc"))
+    else:
+        lab = out.labels.cpu().numpy()[np.argsort(v, kind="stable")]
+        assert out.k_eff == k and np.all(np.diff(lab) >= 0) and lab[-1] == k - 1
+
+
 def test_kmeans1d_special_values(g, orc):
     v = np.array([3.0, -0.0, 0.0, -2.5, 1e-300, -40.0, 7.0, 3.0])
     for k in (1, 3, 6, 8):
