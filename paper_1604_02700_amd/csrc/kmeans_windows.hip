@@ -998,9 +998,10 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
     *solved = 0;
     if (!kmeans_windows_apply(n, ke) || ke > kMaxClusters)
         return hipSuccess;
-    // squares that overflow leave no bound that means anything: every row is
+    // squares that overflow, in a sum or times n, or that lose their last
+    // bits to underflow, leave no bound that means anything: every row is
     // computed
-    if (!(gs.s2 < INFINITY) || !worth_it(gs, n, ke))
+    if (!(gs.s2 > 0x1p-900 && gs.s2 < 0x1p900) || !worth_it(gs, n, ke))
         return hipSuccess;
     // cells of the first round, and rows of a layer: as many as are useful and
     // the scratch holds; with few per cluster the windows do not shrink (one is

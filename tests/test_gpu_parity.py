@@ -519,6 +519,30 @@ def test_kmeans1d_solver(g, orc, monkeypatch, n, k, shape, solver):
         assert out.k_eff == k and np.all(np.diff(lab) >= 0) and lab[-1] == k - 1
 
 
+@pytest.mark.parametrize("e,solver", [(-530, "rows"), (437, "windows"), (439, "rows"),
+                                      (494, "rows"), (497, "rows"), (530, "rows")])
+def test_kmeans1d_extreme_squares(g, monkeypatch, e, solver):
+    """Values scaled by 2^e, the sum of squares S2 being 2^24 for e = 0: it
+    underflows (-530), n S2 overflows (from 493 on), squares of sums do (495), S2
+    itself does (501).  The bounds mean nothing then, so every row is computed,
+    from S2 = 2^900 on.  Up to 494 the scaling is exact, and so the labels and
+    centroids are those of the values as they are."""
+    n, k = 20011, 12
+    rng = np.random.default_rng(8)
+    v = np.concatenate([rng.standard_normal(n // 2),
+                        np.floor(40.0 * rng.standard_normal(n - n // 2))])
+    out, took = _kmeans_solver(g, monkeypatch, v, k)
+    assert took == "windows"
+    big, took = _kmeans_solver(g, monkeypatch, np.ldexp(v, e), k)
+    assert took == solver and big.k_eff == k
+    lab = big.labels.cpu().numpy()
+    assert np.all(np.diff(lab[np.argsort(v, kind="stable")]) >= 0)
+    if 0 < e <= 494:
+        assert np.array_equal(lab, out.labels.cpu().numpy())
+        assert np.array_equal(big.centroids.cpu().numpy(),
+                              np.ldexp(out.centroids.cpu().numpy(), e))
+
+
 def test_kmeans1d_special_values(g, orc):
     v = np.array([3.0, -0.0, 0.0, -2.5, 1e-300, -40.0, 7.0, 3.0])
     for k in (1, 3, 6, 8):
