@@ -7,7 +7,7 @@ state in float64; the oracle is float64 throughout.
 import numpy as np
 import pytest
 
-from gpu_helpers import (cosine_tolerance, EPS32, affinity_tolerance, check_kmeans,
+from gpu_helpers import (Filled, cosine_tolerance, EPS32, affinity_tolerance, check_kmeans,
                          check_labels, matched_agreement, rel_l1, stop_margin)
 
 pytestmark = pytest.mark.gpu
@@ -39,20 +39,6 @@ def _t(a):
 def scratch(g, monkeypatch):
     """scratch(x): from now on every buffer the binding allocates (workspaces
     and outputs) holds the float64 x throughout before the call."""
-    class Filled:
-        def __init__(self, x):
-            self.x = x
-
-        def __getattr__(self, name):
-            return getattr(torch, name)
-
-        def empty(self, *a, **kw):
-            t = torch.empty(*a, **kw)
-            if t.is_cuda and t.numel() * t.element_size() >= 8:
-                b = t.view(-1).view(torch.uint8)
-                b[:b.numel() // 8 * 8].view(torch.float64).fill_(self.x)
-            return t
-
     return lambda x: monkeypatch.setattr(g, "torch", Filled(x))
 
 
