@@ -57,6 +57,7 @@
 // two points play different parts in the Gram form); the symmetric modes
 // use the value computed with the earlier point as the row.
 #include "common.h"
+#include "lanes.h"
 
 #include <type_traits>
 
@@ -1047,24 +1048,6 @@ constexpr int kVsLaneRows = 8;
 // rows of a lane evaluated together (4 need spills above 8 coordinates)
 constexpr int vs_step(int d) { return d <= 8 ? 4 : 2; }
 
-// The float64 of lane (lane xor K), K = 1, 2 (data-parallel moves) or 4 (a
-// swizzle), on the two halves of the value.
-template <int K>
-__device__ __forceinline__ double xor_lane(double x)
-{
-    const long long b = __double_as_longlong(x);
-    int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
-    if (K == 4) {
-        lo = __builtin_amdgcn_ds_swizzle(lo, 0x101f);
-        hi = __builtin_amdgcn_ds_swizzle(hi, 0x101f);
-    } else {
-        constexpr int ctrl = (K == 1) ? 0xb1 : 0x4e;
-        lo = __builtin_amdgcn_mov_dpp(lo, ctrl, 0xf, 0xf, false);
-        hi = __builtin_amdgcn_mov_dpp(hi, ctrl, 0xf, 0xf, false);
-    }
-    return __longlong_as_double(((long long)(unsigned)hi << 32) | (long long)(unsigned)lo);
-}
-
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void affinity_valu_sym_kernel(
     const float *__restrict__ X, int64_t n, float c, int64_t chunk_cols,
@@ -1183,12 +1166,12 @@ __global__ __launch_bounds__(kThreads, 2) void affinity_valu_sym_kernel(
                 for (int q = 0; q < 2; ++q) {
                     const double send = b0 ? cs[q] : cs[q + 2];
                     const double keep = b0 ? cs[q + 2] : cs[q];
-                    h[q] = keep + xor_lane<1>(send);
+                    h[q] = keep + lane_xor<1>(send);
                 }
                 const double send = b1 ? h[0] : h[1];
                 const double keep = b1 ? h[1] : h[0];
-                double t = keep + xor_lane<2>(send);
-                t = t + xor_lane<4>(t);
+                double t = keep + lane_xor<2>(send);
+                t = t + lane_xor<4>(t);
                 if (rl < 4)
                     cred[buf][wave][cb + 2 * (rl & 1) + (rl >> 1)] = t;
             }
@@ -1628,17 +1611,17 @@ hipError_t launch_fused_apply(const float *X, int64_t n, int d, float c,
         }
 #undef GPIC_VALU
     } else {
-#define GPIC_MFMA(NCH)                                                                \
-    launch_engine<NCH, kApplySym>(w, n, chunk_cols, nchunks, nullptr, 0, v, degree,   \
+#define GPIC_MFMA(NCH)                                                                    \
+    launch_engine<NCH, kApplySym>(w, n, chunk_cols, nchunks, nullptr, 0, v, degree,       \
                                   nullptr, w.part, nullptr, ctl, uc, s, colpart)
-    switch (nch_for(d)) {
-    case 1: GPIC_MFMA(1); break;
-    case 2: GPIC_MFMA(2); break;
-    case 3: GPIC_MFMA(3); break;
-    default: GPIC_MFMA(4); break;
-    }
+        switch (nch_for(d)) {
+        case 1: GPIC_MFMA(1); break;
+        case 2: GPIC_MFMA(2); break;
+        case 3: GPIC_MFMA(3); break;
+        default: GPIC_MFMA(4); break;
+        }
 #undef GPIC_MFMA
-    G = rows_per_group(kApplySym, nch_for(d));
+        G = rows_per_group(kApplySym, nch_for(d));
     }
     hipLaunchKernelGGL(fused_sym_reduce_kernel, dim3((unsigned)fused_blocks(n, d)),
                        dim3(kThreads), 0, s, w.part, nchunks, chunk_cols, colpart, n, G, degree,

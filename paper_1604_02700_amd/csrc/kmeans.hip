@@ -1087,28 +1087,28 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
                            P, idxA, sv, run, sc, SS);
         GPIC_TRY(hipGetLastError());
     } else {
-    // 1. radix sort
-    hipLaunchKernelGGL(make_keys_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
-                       v, n, keyA, idxA);
-    // (its histogram in the sorted values' place and its block sums in the
-    // prefix sums', 8n and 16n bytes that are written after the sort)
-    GPIC_TRY(radix_sort_u64(keyA, idxA, keyB, idxB, n, 64, (uint32_t *)sv, (uint32_t *)SS, s,
-                            true));
-    GPIC_TRY(hipGetLastError());
+        // 1. radix sort
+        hipLaunchKernelGGL(make_keys_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
+                           v, n, keyA, idxA);
+        // (its histogram in the sorted values' place and its block sums in the
+        // prefix sums', 8n and 16n bytes that are written after the sort)
+        GPIC_TRY(radix_sort_u64(keyA, idxA, keyB, idxB, n, 64, (uint32_t *)sv, (uint32_t *)SS, s,
+                                true));
+        GPIC_TRY(hipGetLastError());
 
-    // 2. values, runs, mean, prefix sums
-    hipLaunchKernelGGL(decode_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s, keyA,
-                       n, sv, run, t1, t2);
-    hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1024), 0, s, t1, t2, nt, n, sc,
-                       windows ? &sc->gaps : (GapStats *)nullptr);
-    hipLaunchKernelGGL(tile_moments_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s,
-                       sv, n, sc, t1, t2);
-    hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(kScanThreads), 0, s, t1, t2, nt);
-    hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s, sv,
-                       n, sc, t1, t2, SS);
-    GPIC_TRY(hipGetLastError());
-    if (windows)
-        GPIC_TRY(launch_gap_stats(sv, SS, n, &sc->gaps, s));
+        // 2. values, runs, mean, prefix sums
+        hipLaunchKernelGGL(decode_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s, keyA,
+                           n, sv, run, t1, t2);
+        hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1024), 0, s, t1, t2, nt, n, sc,
+                           windows ? &sc->gaps : (GapStats *)nullptr);
+        hipLaunchKernelGGL(tile_moments_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s,
+                           sv, n, sc, t1, t2);
+        hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(kScanThreads), 0, s, t1, t2, nt);
+        hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)nt), dim3(kThreads), 0, s, sv,
+                           n, sc, t1, t2, SS);
+        GPIC_TRY(hipGetLastError());
+        if (windows)
+            GPIC_TRY(launch_gap_stats(sv, SS, n, &sc->gaps, s));
     }
     KmScalars hsc{};
     GPIC_TRY(hipMemcpyAsync(&hsc, sc, scalars_bytes(n, k), hipMemcpyDeviceToHost, s));
@@ -1125,127 +1125,127 @@ hipError_t run_kmeans1d(const double *v, int64_t n, int32_t k, int32_t *labels,
                                 (double *)(w + L.psum), w + L.opt, L.qlen - L.opt, first, s,
                                 &solved));
     if (!solved) {
-    hipLaunchKernelGGL(first_layer_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
-                       SS, run, n, Ea, Q.qlen);
-    const int F = fary_f(n);
-    // levels of the F-ary recursion: until every interval has <= F rows
-    int levels = 1;
-    for (int64_t m = n; m > F; m /= (F + 1))       // gaps hold <= m / (F+1) rows
-        ++levels;
-    if (levels > kMaxLevels)
-        return hipErrorInvalidValue;               // not reachable for n <= 2^30
-    double *Ep = Ea, *Ec = Eb;
-    if (ke > 1) {
-        // samples per level, from the interval sizes alone (each level's
-        // intervals take at most a few distinct sizes)
-        int64_t count[kMaxLevels] = {};
-        {
-            int64_t sz[64], mult[64];
-            int ns = 1;
-            sz[0] = n;
-            mult[0] = 1;
-            int64_t total = 0;
-            for (int Lv = 0; Lv < levels; ++Lv) {
-                int64_t nsz[64], nmult[64];
-                int nn = 0;
-                auto add = [&](int64_t m, int64_t c) {
-                    if (m <= 0)
-                        return true;
-                    for (int u = 0; u < nn; ++u)
-                        if (nsz[u] == m) {
-                            nmult[u] += c;
+        hipLaunchKernelGGL(first_layer_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
+                           SS, run, n, Ea, Q.qlen);
+        const int F = fary_f(n);
+        // levels of the F-ary recursion: until every interval has <= F rows
+        int levels = 1;
+        for (int64_t m = n; m > F; m /= (F + 1))       // gaps hold <= m / (F+1) rows
+            ++levels;
+        if (levels > kMaxLevels)
+            return hipErrorInvalidValue;               // not reachable for n <= 2^30
+        double *Ep = Ea, *Ec = Eb;
+        if (ke > 1) {
+            // samples per level, from the interval sizes alone (each level's
+            // intervals take at most a few distinct sizes)
+            int64_t count[kMaxLevels] = {};
+            {
+                int64_t sz[64], mult[64];
+                int ns = 1;
+                sz[0] = n;
+                mult[0] = 1;
+                int64_t total = 0;
+                for (int Lv = 0; Lv < levels; ++Lv) {
+                    int64_t nsz[64], nmult[64];
+                    int nn = 0;
+                    auto add = [&](int64_t m, int64_t c) {
+                        if (m <= 0)
                             return true;
+                        for (int u = 0; u < nn; ++u)
+                            if (nsz[u] == m) {
+                                nmult[u] += c;
+                                return true;
+                            }
+                        if (nn == 64)
+                            return false;
+                        nsz[nn] = m;
+                        nmult[nn++] = c;
+                        return true;
+                    };
+                    for (int u = 0; u < ns; ++u) {
+                        const int64_t m = sz[u], c = mult[u];
+                        if (m <= F) {
+                            count[Lv] += m * c;
+                            continue;
                         }
-                    if (nn == 64)
-                        return false;
-                    nsz[nn] = m;
-                    nmult[nn++] = c;
-                    return true;
-                };
-                for (int u = 0; u < ns; ++u) {
-                    const int64_t m = sz[u], c = mult[u];
-                    if (m <= F) {
-                        count[Lv] += m * c;
-                        continue;
+                        count[Lv] += (int64_t)F * c;
+                        int32_t prev = -1;
+                        for (int f = 0; f <= F; ++f) {
+                            const int32_t sr = (f < F)
+                                ? (F == kFSmall ? sample_row<kFSmall>(0, (int32_t)m - 1, f)
+                                                : sample_row<kFLarge>(0, (int32_t)m - 1, f))
+                                : (int32_t)m;
+                            if (!add(sr - prev - 1, c))
+                                return hipErrorInvalidValue;
+                            prev = sr;
+                        }
                     }
-                    count[Lv] += (int64_t)F * c;
-                    int32_t prev = -1;
-                    for (int f = 0; f <= F; ++f) {
-                        const int32_t sr = (f < F)
-                            ? (F == kFSmall ? sample_row<kFSmall>(0, (int32_t)m - 1, f)
-                                            : sample_row<kFLarge>(0, (int32_t)m - 1, f))
-                            : (int32_t)m;
-                        if (!add(sr - prev - 1, c))
-                            return hipErrorInvalidValue;
-                        prev = sr;
+                    total += count[Lv];
+                    ns = nn;
+                    for (int u = 0; u < nn; ++u) {
+                        sz[u] = nsz[u];
+                        mult[u] = nmult[u];
                     }
                 }
-                total += count[Lv];
-                ns = nn;
-                for (int u = 0; u < nn; ++u) {
-                    sz[u] = nsz[u];
-                    mult[u] = nmult[u];
+                if (total != n || ns != 0)
+                    return hipErrorInvalidValue;       // the recursion does not cover every row
+            }
+            RowEntry *ent = (RowEntry *)(w + L.ent), *list = (RowEntry *)(w + L.list);
+            int32_t *lr = (int32_t *)(w + L.lr), *bh = (int32_t *)(w + L.bh);
+            int32_t *lbase = (int32_t *)(w + L.lbase);
+            // two clusters need the last layer's one row only
+            if (ke > 2 && F == kFSmall)
+                hipLaunchKernelGGL(row_level_kernel<kFSmall>, dim3(blocks_for(n)), dim3(kThreads),
+                                   0, s, (int32_t)n, levels, ent, lr, bh);
+            else if (ke > 2)
+                hipLaunchKernelGGL(row_level_kernel<kFLarge>, dim3(blocks_for(n)), dim3(kThreads),
+                                   0, s, (int32_t)n, levels, ent, lr, bh);
+            if (ke > 2) {
+                hipLaunchKernelGGL(level_scan_kernel, dim3(1), dim3(1024), 0, s, bh,
+                                   (int64_t)blocks_for(n), levels, lbase);
+                hipLaunchKernelGGL(level_scatter_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
+                                   (int32_t)n, ent, lr, bh, lbase, list);
+            }
+            int g = 0;                                 // levels run so far
+            for (int c = 1; c < ke; ++c) {
+                int32_t *oc = opt + (int64_t)c * n;
+                if (c == ke - 1) {
+                    // only row n - 1 of the last layer is read
+                    const int64_t want = (n - 1 + kThreads - 1) / kThreads;
+                    const int nbl = (int)(want < kLastBlocks ? want : kLastBlocks);
+                    hipLaunchKernelGGL(last_row_kernel, dim3(nbl), dim3(kThreads), 0, s, SS, Ep,
+                                       n, Q.pbest, Q.parg);
+                    hipLaunchKernelGGL(last_row_merge_kernel, dim3(1), dim3(kWave), 0, s,
+                                       (const double *)Q.pbest, (const int32_t *)Q.parg, nbl, n,
+                                       oc);
+                    break;
                 }
-            }
-            if (total != n || ns != 0)
-                return hipErrorInvalidValue;       // the recursion does not cover every row
-        }
-        RowEntry *ent = (RowEntry *)(w + L.ent), *list = (RowEntry *)(w + L.list);
-        int32_t *lr = (int32_t *)(w + L.lr), *bh = (int32_t *)(w + L.bh);
-        int32_t *lbase = (int32_t *)(w + L.lbase);
-        // two clusters need the last layer's one row only
-        if (ke > 2 && F == kFSmall)
-            hipLaunchKernelGGL(row_level_kernel<kFSmall>, dim3(blocks_for(n)), dim3(kThreads),
-                               0, s, (int32_t)n, levels, ent, lr, bh);
-        else if (ke > 2)
-            hipLaunchKernelGGL(row_level_kernel<kFLarge>, dim3(blocks_for(n)), dim3(kThreads),
-                               0, s, (int32_t)n, levels, ent, lr, bh);
-        if (ke > 2) {
-            hipLaunchKernelGGL(level_scan_kernel, dim3(1), dim3(1024), 0, s, bh,
-                               (int64_t)blocks_for(n), levels, lbase);
-            hipLaunchKernelGGL(level_scatter_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s,
-                               (int32_t)n, ent, lr, bh, lbase, list);
-        }
-        int g = 0;                                 // levels run so far
-        for (int c = 1; c < ke; ++c) {
-            int32_t *oc = opt + (int64_t)c * n;
-            if (c == ke - 1) {
-                // only row n - 1 of the last layer is read
-                const int64_t want = (n - 1 + kThreads - 1) / kThreads;
-                const int nbl = (int)(want < kLastBlocks ? want : kLastBlocks);
-                hipLaunchKernelGGL(last_row_kernel, dim3(nbl), dim3(kThreads), 0, s, SS, Ep,
-                                   n, Q.pbest, Q.parg);
-                hipLaunchKernelGGL(last_row_merge_kernel, dim3(1), dim3(kWave), 0, s,
-                                   (const double *)Q.pbest, (const int32_t *)Q.parg, nbl, n,
-                                   oc);
-                break;
-            }
-            for (int Lv = 0; Lv < levels; ++Lv, ++g) {
-                const dim3 grid(blocks_for(count[Lv] > 0 ? count[Lv] : 1));
-                const int whole = count[Lv] <= 512;    // few intervals, many parts each
-                if (F == kFSmall) {
-                    hipLaunchKernelGGL(fary_rows_kernel<kFSmall>, grid, dim3(kThreads), 0, s,
-                                       SS, run, Ep, Ec, oc, (int32_t)n, list, lbase,
-                                       Lv, Q, g);
-                    hipLaunchKernelGGL(fary_queue_kernel<kFSmall>, dim3(2048), dim3(kThreads),
-                                       0, s, SS, run, Ep, Ec, oc, (int32_t)n, Q, g);
-                    hipLaunchKernelGGL(fary_merge_kernel<kFSmall>, dim3(512), dim3(kThreads),
-                                       0, s, Ec, run, (int32_t)n, oc, Q, g, whole);
-                } else {
-                    hipLaunchKernelGGL(fary_rows_kernel<kFLarge>, grid, dim3(kThreads), 0, s,
-                                       SS, run, Ep, Ec, oc, (int32_t)n, list, lbase,
-                                       Lv, Q, g);
-                    hipLaunchKernelGGL(fary_queue_kernel<kFLarge>, dim3(2048), dim3(kThreads),
-                                       0, s, SS, run, Ep, Ec, oc, (int32_t)n, Q, g);
-                    hipLaunchKernelGGL(fary_merge_kernel<kFLarge>, dim3(512), dim3(kThreads),
-                                       0, s, Ec, run, (int32_t)n, oc, Q, g, whole);
+                for (int Lv = 0; Lv < levels; ++Lv, ++g) {
+                    const dim3 grid(blocks_for(count[Lv] > 0 ? count[Lv] : 1));
+                    const int whole = count[Lv] <= 512;    // few intervals, many parts each
+                    if (F == kFSmall) {
+                        hipLaunchKernelGGL(fary_rows_kernel<kFSmall>, grid, dim3(kThreads), 0, s,
+                                           SS, run, Ep, Ec, oc, (int32_t)n, list, lbase,
+                                           Lv, Q, g);
+                        hipLaunchKernelGGL(fary_queue_kernel<kFSmall>, dim3(2048), dim3(kThreads),
+                                           0, s, SS, run, Ep, Ec, oc, (int32_t)n, Q, g);
+                        hipLaunchKernelGGL(fary_merge_kernel<kFSmall>, dim3(512), dim3(kThreads),
+                                           0, s, Ec, run, (int32_t)n, oc, Q, g, whole);
+                    } else {
+                        hipLaunchKernelGGL(fary_rows_kernel<kFLarge>, grid, dim3(kThreads), 0, s,
+                                           SS, run, Ep, Ec, oc, (int32_t)n, list, lbase,
+                                           Lv, Q, g);
+                        hipLaunchKernelGGL(fary_queue_kernel<kFLarge>, dim3(2048), dim3(kThreads),
+                                           0, s, SS, run, Ep, Ec, oc, (int32_t)n, Q, g);
+                        hipLaunchKernelGGL(fary_merge_kernel<kFLarge>, dim3(512), dim3(kThreads),
+                                           0, s, Ec, run, (int32_t)n, oc, Q, g, whole);
+                    }
                 }
+                double *tmp = Ep; Ep = Ec; Ec = tmp;
             }
-            double *tmp = Ep; Ep = Ec; Ec = tmp;
         }
-    }
-    GPIC_TRY(hipGetLastError());
-    hipLaunchKernelGGL(backtrack_kernel, dim3(1), dim3(64), 0, s, opt, n, ke, first);
+        GPIC_TRY(hipGetLastError());
+        hipLaunchKernelGGL(backtrack_kernel, dim3(1), dim3(64), 0, s, opt, n, ke, first);
     }
 
     // 4. cluster statistics, labels

@@ -34,7 +34,7 @@
 //      from float64 distances.
 // Supports d <= 16 and k <= 64.
 #include "common.h"
-#include "kmeans_dev.h"
+#include "lanes.h"
 
 namespace gpic {
 namespace {
