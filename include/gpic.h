@@ -267,10 +267,10 @@ gpic_status gpic_degree_normalize_csr(const int64_t *row_ptr,
 
 /* Fused (W never stored): d_i = sum_{j != i} A_ij with A recomputed from the
  * points as in gpic_affinity, and v0 = D / sum D.  Nothing of size n^2 is
- * written.  For 16 <= d <= 128 and n <= 2^19 (d < 16: 10,000 <= n <= 2^19)
- * the fused operator evaluates each pair {i, j} once (A = A^T, section
- * "Spectral Cluster") and uses that one float32 value for both A_ij and
- * A_ji; the degrees are the row sums of that same symmetric A (so W's rows
+ * written.  For 16 <= d <= 128 and n <= 2^19 (d < 16: from n = 10,000 on,
+ * d = 1 from 14,000) the fused operator evaluates each pair {i, j} once
+ * (A = A^T, section "Spectral Cluster") and uses that one float32 value for
+ * both A_ij and A_ji; the degrees are the row sums of that same symmetric A (so W's rows
  * sum to 1 up to float64 rounding), and may differ from gpic_affinity's row
  * sums in the last float32 bits of individual entries (d >= 16) and in the
  * order of the float64 sums.  ws: gpic_workspace_bytes(GPIC_OP_DEGREE_FUSED, n, 0, 0)

@@ -1291,13 +1291,18 @@ int64_t padded_points(int64_t n) { return (n + kColAlign - 1) / kColAlign * kCol
 // the product sums whole rows.
 constexpr int64_t kFusedSymMaxN = 1 << 19;
 
-// Below 16 dimensions from 10,000 points on: with fewer the (256 rows, chunk)
-// pieces leave much of the chip idle (per product at n = 8,000, d = 2, 5, 8:
-// 32, 42, 52 us against 28, 38, 51 with every ordered pair; at 20,000: 100,
-// 140, 176 against 130, 181, 252).
-constexpr int64_t kValuSymMinN = 10000;
+// Below 16 dimensions from 10,000 points on, in one dimension from 14,000:
+// with fewer the (256 rows, chunk) pieces leave much of the chip idle.  Ten
+// updates, us, against every ordered pair: n = 10,000, d = 1, 2, 5, 8, 15: 557,
+// 515, 631, 751, 1,159 against 488, 526, 673, 876, 1,616; n = 12,000, d = 1, 2: 646,
+// 583 against 602, 654; 14,000: 705, 647 against 724, 805.  n = 8,000, one
+// product, d = 2, 5, 8: 32, 42, 52 against 28, 38, 51.
+constexpr int64_t kValuSymMinN = 10000, kValuSymMinN1 = 14000;
 
-bool valu_sym(int64_t n, int d) { return d < 16 && n >= kValuSymMinN && n <= kFusedSymMaxN; }
+bool valu_sym(int64_t n, int d)
+{
+    return d < 16 && n >= (d == 1 ? kValuSymMinN1 : kValuSymMinN) && n <= kFusedSymMaxN;
+}
 bool fused_sym(int64_t n, int d)
 {
     return (use_mfma(d) && n <= kFusedSymMaxN) || valu_sym(n, d);

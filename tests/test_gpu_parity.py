@@ -645,6 +645,21 @@ def test_fused_loop_few_dimensions(g, orc, scratch, n, d):
     assert rel_l1(job.pi.v.cpu().numpy(), w.cpu().numpy()) <= 1e-10
 
 
+@pytest.mark.parametrize("n,d,once", [(13999, 1, False), (14000, 1, True), (9999, 2, False),
+                                      (10000, 2, True)])
+def test_fused_few_dimensions_switch(g, orc, n, d, once):
+    """Where each pair is evaluated once.  The full rows add in the order of
+    gpic_affinity's degrees, so these are the same bits; row and column sums
+    are not, and agree to float64 rounding."""
+    X = _pts(n, d, 11, scale=1.2)
+    deg, _, _ = g.gpic_degree_fused(_t(X), np.float32(0.8))
+    _, dense = g.gpic_affinity(_t(X), np.float32(0.8))
+    assert torch.equal(deg, dense) == (not once)
+    np.testing.assert_allclose(deg.cpu().numpy(), dense.cpu().numpy(), rtol=1e-13)
+    dr, _, _ = orc.degree_onthefly(X, np.float32(0.8))
+    np.testing.assert_allclose(deg.cpu().numpy(), dr, rtol=1e-5)
+
+
 def test_fused_few_dimensions_far_point(g):
     """An infinite coordinate in the last point (whose tile is padded): its
     own degree is 0 and no other row notices."""
