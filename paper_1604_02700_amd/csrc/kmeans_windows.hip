@@ -76,6 +76,7 @@ constexpr int kMaxPer = 1024;            // cells per layer of a window later
 constexpr int kMaxMerged = 8;            // a layer's range: up to this many times as many
 constexpr int kMaxClusters = 512;
 constexpr int kMaxRounds = 5;
+constexpr int kMaxPoints = 1 << 17;      // of a grid; the rules below keep to 88,200
 
 // What a round leaves for the host.
 struct RoundCtl {
@@ -646,6 +647,8 @@ __device__ __forceinline__ int32_t block_scan_incl(int32_t x, int32_t *a)
 // that of the cells it keeps, made monotone over the layers; what lies in it
 // between windows is left out, so that a few far apart ways to place the
 // cuts (k above the number of clusters) do not keep all that lies between.
+// One workgroup, bound by the latency of its few dependent passes: 20-30 us
+// for 50,000 points (the marks read a thread's run of points at a time: 119).
 constexpr int kWinThreads = 1024;
 static_assert(kMaxClusters <= kWinThreads, "a thread per layer");
 
@@ -653,6 +656,7 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
 {
     __shared__ int32_t a[kWinThreads];
     __shared__ int32_t lo[kMaxClusters], hi[kMaxClusters];
+    __shared__ uint64_t cm[kMaxPoints / 64], pm[kMaxPoints / 64];
     __shared__ int32_t split, extra, rows, fail, all, exact;
     const int t = threadIdx.x;
     const int c = t;                             // the thread's layer, if any
@@ -685,54 +689,68 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
         }
         __syncthreads();
     }
-    // windows, kept cells and their positions before a thread's grid points
+    // the marks of the grid points, 64 to a word, a wave's loads at a time
     const int32_t n = V.ctl->total;
-    const int32_t per = (n + kWinThreads - 1) / kWinThreads;
-    const int32_t i0 = t * per, i1 = min(i0 + per, n);
-    int32_t s = 0, m = 0, k = 0, l = 0;
-    bool left = i0 > 0 && i0 < i1 && V.keepc[i0 - 1] != 0;
-    for (int32_t i = i0; i < i1; ++i) {
-        const bool cell = V.keepc[i] != 0;
-        s += (cell || V.keepp[i] != 0) && !left;
-        m += cell && !left;
-        if (cell) {
-            ++k;
-            l += V.pos[i + 1] - V.pos[i];
+    const int32_t words = (n + 63) / 64;
+#pragma unroll 4
+    for (int32_t i = t; i < words * 64; i += kWinThreads) {
+        const uint64_t c64 = __ballot(i < n && V.keepc[i] != 0);
+        const uint64_t p64 = __ballot(i < n && V.keepp[i] != 0);
+        if (t % kWave == 0) {
+            cm[i / 64] = c64;
+            pm[i / 64] = p64;
         }
-        left = cell;
     }
-    int32_t ws = block_scan_incl<kWinThreads>(s, a);
+    __syncthreads();
+    // windows, kept cells and their positions before a thread's words: bits
+    // where a window starts (a cell or point without a kept cell before it)
+    // and ends, in turn
+    const int32_t per = (words + kWinThreads - 1) / kWinThreads;
+    const int32_t w0 = t * per, w1 = min(w0 + per, words);
+    int32_t ws = 0, wm = 0, wk = 0, wl = 0;
+    auto walk = [&](auto &&start, auto &&end) {
+        for (int32_t w = w0; w < w1; ++w) {
+            const uint64_t C = cm[w], before = (C << 1) | (w > 0 ? cm[w - 1] >> 63 : 0);
+            const uint64_t in = C | pm[w] | before;
+            const uint64_t first = in & ~before, last = in & ~C;
+            int32_t open = (before & 1) ? V.pos[w * 64] : 0;
+            for (uint64_t e = first | last; e != 0; e &= e - 1) {
+                const int b = __ffsll((unsigned long long)e) - 1;
+                const int32_t p = V.pos[w * 64 + b];
+                if ((first >> b) & 1) {
+                    start(p, __popcll(C & ((1ull << b) - 1)));
+                    ++ws;
+                    wm += (int)((C >> b) & 1);
+                    open = p;
+                }
+                if ((last >> b) & 1) {
+                    end(p);
+                    wl += p - open;
+                }
+            }
+            if (C >> 63)
+                wl += V.pos[w * 64 + 64] - open;
+            wk += __popcll(C);
+        }
+    };
+    walk([](int32_t, int) {}, [](int32_t) {});
+    const int32_t s = ws, m = wm, k = wk, l = wl;
+    ws = block_scan_incl<kWinThreads>(s, a) - s;
     const int32_t nseg = a[kWinThreads - 1];
-    int32_t wm = block_scan_incl<kWinThreads>(m, a);
+    wm = block_scan_incl<kWinThreads>(m, a) - m;
     const int32_t wide = a[kWinThreads - 1];
-    int32_t wk = block_scan_incl<kWinThreads>(k, a);
+    wk = block_scan_incl<kWinThreads>(k, a) - k;
     const int32_t cells = a[kWinThreads - 1];
-    int32_t wl = block_scan_incl<kWinThreads>(l, a);
+    wl = block_scan_incl<kWinThreads>(l, a) - l;
     const int32_t span = a[kWinThreads - 1] + nseg;
-    ws -= s;
-    wm -= m;
-    wk -= k;
-    wl -= l;
-    left = i0 > 0 && i0 < i1 && V.keepc[i0 - 1] != 0;
-    for (int32_t i = i0; i < i1; ++i) {
-        const bool cell = V.keepc[i] != 0;
-        const bool in = cell || V.keepp[i] != 0 || left;
-        if (in && !left) {
-            V.segP[ws] = V.pos[i];
-            V.kpre[ws] = wk;
+    walk(
+        [&](int32_t p, int below) {
+            V.segP[ws] = p;
+            V.kpre[ws] = wk + below;
             V.lpre[ws] = wl + ws;
             V.mpre[ws] = wm;
-            ++ws;
-            wm += cell;
-        }
-        if (in && !cell)
-            V.segQ[ws - 1] = V.pos[i];
-        if (cell) {
-            ++wk;
-            wl += V.pos[i + 1] - V.pos[i];
-        }
-        left = cell;
-    }
+        },
+        [&](int32_t p) { V.segQ[ws - 1] = p; });
     if (t == 0) {
         V.kpre[nseg] = cells;
         V.lpre[nseg] = span;
@@ -1022,6 +1040,8 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
     if (per < 32 || per < 2 * ke || (cells < (double)n && cells < 10.0 * ke * sqrt((double)ke)))
         return hipSuccess;
     place(static_cast<char *>(ws), n, ke, per, merged, &V);
+    if (V.points > kMaxPoints)
+        return hipSuccess;                           // not reached
     V.sv = sv;
     V.run = run;
     V.SS = SS;
