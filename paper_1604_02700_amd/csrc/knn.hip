@@ -213,10 +213,13 @@ __global__ __launch_bounds__(kThreads) void knn_bound_kernel(
 // from the point to the box centres as in near_tiles_kernel, then the k-th
 // smallest of the distances to their 2,048 points by bisection on the bit
 // patterns.  A wide bound costs its whole row tile a visit to most of a
-// cluster: n = 2M, d = 8, k = 32, ms per graph here and in the collection
-// with kWide = 4: 11 and 60, 6: 6 and 64, and (one workgroup per row tile)
-// 3: 39 and 57, 12: 18 and 75, without the pass before the first
-// collection: 12 and 85.
+// cluster.  ms per graph with kWide = 3, 6, 12: n = 2M, d = 8, k = 32: 141, 128,
+// 135; d = 2, k = 5: 71, 30, 18; n = 200,000, d = 2, 8, 16 with k = 5: 4.3, 2.9,
+// 2.5; 6.4, 4.5, 6.0; 7.2, 9.9, 9.7; with k = 32: 4.5, 4.4, 4.4; 10.6, 11.4, 11.6;
+// 14.5, 15.2, 15.6; with k = 64 within 7 %; half of the points in 1,560 places, d
+// = 6, k = 10: 10.2, 12.1, 13.9.  kNear = 16, 32, 64 at the first: 134, 128, 129;
+// at the others 16 is up to 10 % faster and 64 up to 28 % slower, at n =
+// 20,000, d = 16, k = 64: 2.9, 3.3, 4.0.
 constexpr float kWide = 6.0f;
 constexpr unsigned kRefineParts = 4;   // workgroups per row tile, each every 4th row
 
@@ -533,8 +536,9 @@ __device__ __forceinline__ float box_gap2(float lo, float hi, float rlo, float r
 // until the end.  Bound by the matrix cores and the comparison of their
 // results (1,260 tiles of 64 visited per row tile at n = 2M, d = 8, k = 32
 // before the blocks' boxes, which leave 0.57 of the pairs).  Per graph there:
-// 101 ms; 92 with the counters in LDS; 64 with tighter bounds, coordinate-
-// major boxes and the blocks.
+// 101 ms; 92 with the counters in LDS; 64 to 73, box to box, with tighter
+// bounds, coordinate-major boxes and the blocks (52 for all rows, the rest
+// for those whose lists overflowed).
 template <int KS>
 __global__ __launch_bounds__(kThreads) void knn_collect_kernel(
     const float *__restrict__ xa, int64_t np, const float *__restrict__ xb, int64_t n, int d,
