@@ -63,7 +63,9 @@ constexpr int kWaves = kThreads / kWave;
 // 1.3 times (fewer clusters than k, of widths 1e-2 to 1e-10, the cost near the
 // rounding), n = 30,000 and 40,000 with k = 10 up to 1.09.
 // Cells: a first round of 1,024 costs 0.1-0.3 ms more, of 256 leaves wider
-// windows; rows of 4 x kMaxPer instead of 8 x lose from k = 50 on.
+// windows; rows of 4 x kMaxPer instead of 8 x lose from k = 50 on.  Splits by 4,
+// 8, 16 and as many as fit: the clustering's embeddings at n = 2M, k = 50: 3.23,
+// 3.45, 3.67, 3.67 ms; by 4 some values no longer shrink (n = 1,050,000, k = 70).
 constexpr int64_t kFromN = 8192, kLargeN = (int64_t)1 << 17, kHugeN = (int64_t)1 << 18;
 constexpr int kFewSmall = 10, kFewLarge = 7, kFewHuge = 3;   // clusters below, from kLargeN, kHugeN
 // Costs of spare cuts up to this many times the bound on the rounding leave
@@ -75,6 +77,7 @@ constexpr int kFirst = 512;              // cells of the first round
 constexpr int kMaxPer = 1024;            // cells per layer of a window later
 constexpr int kMaxMerged = 8;            // a layer's range: up to this many times as many
 constexpr int kMaxClusters = 512;
+constexpr int kMaxSplit = 8;             // cells of one that is kept, beside a window's share
 constexpr int kMaxRounds = 5;
 constexpr int kMaxPoints = 1 << 17;      // of a grid; the rules below keep to 88,200
 
@@ -647,8 +650,8 @@ __device__ __forceinline__ int32_t block_scan_incl(int32_t x, int32_t *a)
 // that of the cells it keeps, made monotone over the layers; what lies in it
 // between windows is left out, so that a few far apart ways to place the
 // cuts (k above the number of clusters) do not keep all that lies between.
-// One workgroup, bound by the latency of its few dependent passes: 20-30 us
-// for 50,000 points (the marks read a thread's run of points at a time: 119).
+// One workgroup, bound by the latency of its few dependent passes: 16 us for
+// 513 points, 52 for 49,000 (119 with a thread's run of marks read at a time).
 constexpr int kWinThreads = 1024;
 static_assert(kMaxClusters <= kWinThreads, "a thread per layer");
 
@@ -692,7 +695,7 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
     // the marks of the grid points, 64 to a word, a wave's loads at a time
     const int32_t n = V.ctl->total;
     const int32_t words = (n + 63) / 64;
-#pragma unroll 4
+#pragma unroll 8
     for (int32_t i = t; i < words * 64; i += kWinThreads) {
         const uint64_t c64 = __ballot(i < n && V.keepc[i] != 0);
         const uint64_t p64 = __ballot(i < n && V.keepp[i] != 0);
@@ -702,55 +705,59 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
         }
     }
     __syncthreads();
-    // windows, kept cells and their positions before a thread's words: bits
-    // where a window starts (a cell or point without a kept cell before it)
-    // and ends, in turn
+    // windows and kept cells before a thread's words: a window starts at a cell
+    // or point without a kept cell before it, and ends at one without a cell
     const int32_t per = (words + kWinThreads - 1) / kWinThreads;
     const int32_t w0 = t * per, w1 = min(w0 + per, words);
-    int32_t ws = 0, wm = 0, wk = 0, wl = 0;
-    auto walk = [&](auto &&start, auto &&end) {
-        for (int32_t w = w0; w < w1; ++w) {
-            const uint64_t C = cm[w], before = (C << 1) | (w > 0 ? cm[w - 1] >> 63 : 0);
-            const uint64_t in = C | pm[w] | before;
-            const uint64_t first = in & ~before, last = in & ~C;
-            int32_t open = (before & 1) ? V.pos[w * 64] : 0;
-            for (uint64_t e = first | last; e != 0; e &= e - 1) {
-                const int b = __ffsll((unsigned long long)e) - 1;
-                const int32_t p = V.pos[w * 64 + b];
-                if ((first >> b) & 1) {
-                    start(p, __popcll(C & ((1ull << b) - 1)));
-                    ++ws;
-                    wm += (int)((C >> b) & 1);
-                    open = p;
-                }
-                if ((last >> b) & 1) {
-                    end(p);
-                    wl += p - open;
-                }
-            }
-            if (C >> 63)
-                wl += V.pos[w * 64 + 64] - open;
-            wk += __popcll(C);
-        }
-    };
-    walk([](int32_t, int) {}, [](int32_t) {});
-    const int32_t s = ws, m = wm, k = wk, l = wl;
-    ws = block_scan_incl<kWinThreads>(s, a) - s;
+    auto before = [&](int32_t w) { return (cm[w] << 1) | (w > 0 ? cm[w - 1] >> 63 : 0); };
+    auto starts = [&](int32_t w) { return (cm[w] | pm[w]) & ~before(w); };
+    int32_t s = 0, m = 0, k = 0;
+    for (int32_t w = w0; w < w1; ++w) {
+        const uint64_t first = starts(w);
+        s += __popcll(first);
+        m += __popcll(first & cm[w]);
+        k += __popcll(cm[w]);
+    }
+    int32_t ws = block_scan_incl<kWinThreads>(s, a) - s;
     const int32_t nseg = a[kWinThreads - 1];
-    wm = block_scan_incl<kWinThreads>(m, a) - m;
+    int32_t wm = block_scan_incl<kWinThreads>(m, a) - m;
     const int32_t wide = a[kWinThreads - 1];
-    wk = block_scan_incl<kWinThreads>(k, a) - k;
+    int32_t wk = block_scan_incl<kWinThreads>(k, a) - k;
     const int32_t cells = a[kWinThreads - 1];
-    wl = block_scan_incl<kWinThreads>(l, a) - l;
-    const int32_t span = a[kWinThreads - 1] + nseg;
-    walk(
-        [&](int32_t p, int below) {
-            V.segP[ws] = p;
-            V.kpre[ws] = wk + below;
-            V.lpre[ws] = wl + ws;
-            V.mpre[ws] = wm;
-        },
-        [&](int32_t p) { V.segQ[ws - 1] = p; });
+    // the windows' first and last grid points
+    for (int32_t w = w0; w < w1; ++w) {
+        const uint64_t C = cm[w], first = starts(w), last = (C | pm[w] | before(w)) & ~C;
+        for (uint64_t e = first | last; e != 0; e &= e - 1) {
+            const int b = __ffsll((unsigned long long)e) - 1;
+            if ((first >> b) & 1) {
+                V.segP[ws] = w * 64 + b;
+                V.kpre[ws] = wk + __popcll(C & ((1ull << b) - 1));
+                V.mpre[ws] = wm;
+                ++ws;
+                wm += (int)((C >> b) & 1);
+            }
+            if ((last >> b) & 1)
+                V.segQ[ws - 1] = w * 64 + b;
+        }
+        wk += __popcll(C);
+    }
+    __syncthreads();
+    // their positions, and the positions in the windows before
+    const int32_t wper = (nseg + kWinThreads - 1) / kWinThreads;
+    const int32_t z0 = t * wper, z1 = min(z0 + wper, nseg);
+    int32_t l = 0;
+    for (int32_t z = z0; z < z1; ++z) {
+        const int32_t p = V.pos[V.segP[z]], q = V.pos[V.segQ[z]];
+        V.segP[z] = p;
+        V.segQ[z] = q;
+        l += q - p + 1;
+    }
+    int32_t wl = block_scan_incl<kWinThreads>(l, a) - l;
+    const int32_t span = a[kWinThreads - 1];
+    for (int32_t z = z0; z < z1; ++z) {
+        V.lpre[z] = wl;
+        wl += V.segQ[z] - V.segP[z] + 1;
+    }
     if (t == 0) {
         V.kpre[nseg] = cells;
         V.lpre[nseg] = span;
@@ -792,11 +799,9 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
         }
     }
     __syncthreads();
-    const int64_t f = split, g = extra;
+    const int64_t f = min(split, kMaxSplit), g = extra;
     const bool every = all != 0;
     // the windows' first grid points
-    const int32_t wper = (nseg + kWinThreads - 1) / kWinThreads;
-    const int32_t z0 = t * wper, z1 = min(z0 + wper, nseg);
     auto points = [&](int32_t z) {
         const int32_t len = V.segQ[z] - V.segP[z];
         const int64_t k = V.kpre[z + 1] - V.kpre[z];
