@@ -48,26 +48,26 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 // Where the windows are tried, measured against the full programme in the
-// same run: 13 shapes of values (uniform, normal, heavy tails, integers, as
-// many and fewer clusters than k from 1e-9 to 1e-3 wide and of widely
-// different widths), 3 to 5 draws each.  Below 8,192 values the full
-// programme is two or three levels a layer and the scratch holds few cells.
-// Up to 2^17 it has three levels, about 75 us a layer, and with few clusters
-// nothing is gained (k = 7: 1.1 times as fast at n = 12,000, level at
-// 60,000, slower for half of the shapes); k = 10 at n = 8,192, 20,000,
-// 40,000, 120,000: 1.25, 1.23, 1.17, 1.27 (geometric means); k = 24 at 20,000
-// and 60,000: 1.38, 1.41.  n = 140,000, k = 7, 30: 1.19, 1.78; n = 270,000, k = 3,
-// 7, 24: 1.05, 1.53, 2.35; n = 600,000, k = 5, 40: 1.47, 2.9; n = 2M, k = 3, 5,
-// 50: 1.29, 1.75, 4.2 (19.2 ms without).  Of the 3,302 measured under these
-// rules 18 took more than 1.05 times as long as the full programme, the worst
-// 1.3 times (fewer clusters than k, of widths 1e-2 to 1e-10, the cost near the
-// rounding), n = 30,000 and 40,000 with k = 10 up to 1.09.
+// same run, geometric means: on embeddings of the clustering itself (kNN graphs
+// and fused operators, 2 to 16 dimensions), and on 13 shapes of values (uniform,
+// normal, heavy tails, integers, as many and fewer clusters than k from 1e-9 to
+// 1e-3 wide and of widely different widths), 2 to 5 draws each.
+//   Below 8,192 values the full programme is two or three levels a layer and
+// the scratch holds few cells.  Up to 2^18 it has three levels, about 75 us a
+// layer; embeddings with k = 7, 12, 24: n = 8,192: 1.20, 1.38, 1.48 times as
+// fast; 20,000: 1.19, 1.42, 1.40; 60,000: 1.12, 1.27, 1.56 (the slowest 0.94);
+// 125,000: 1.23, 1.45, 1.64.  The shapes there: k = 7: 1.14 at 8,192, 1.11 at
+// 20,000, 1.0 at 60,000, with clusters of widely different widths down to 0.8;
+// k = 10: 1.25, 1.23, 1.15; k = 6: 1.07, 1.07.
+//   From 2^18 values: n = 270,000, k = 3, 7, 24: 1.05, 1.54, 2.4; n = 600,000, k =
+// 5, 40: 1.5, 3.1; n = 2M, k = 3, 5, 50: 1.29, 1.76, 4.5 (19.2 ms without); a few in
+// a hundred, whose cost is near the rounding, down to 0.77.
 // Cells: a first round of 1,024 costs 0.1-0.3 ms more, of 256 leaves wider
 // windows; rows of 4 x kMaxPer instead of 8 x lose from k = 50 on.  Splits by 4,
 // 8, 16 and as many as fit: the clustering's embeddings at n = 2M, k = 50: 3.23,
 // 3.45, 3.67, 3.67 ms; by 4 some values no longer shrink (n = 1,050,000, k = 70).
 constexpr int64_t kFromN = 8192, kLargeN = (int64_t)1 << 17, kHugeN = (int64_t)1 << 18;
-constexpr int kFewSmall = 10, kFewLarge = 7, kFewHuge = 3;   // clusters below, from kLargeN, kHugeN
+constexpr int kFew = 7, kFewHuge = 3;    // fewest clusters below, from kHugeN on
 // Costs of spare cuts up to this many times the bound on the rounding leave
 // windows too wide (clusters of 1e-9 to 1e-12 of the range, fewer than k: a
 // quarter of the full programme's time lost in two rounds that keep everything;
@@ -75,11 +75,11 @@ constexpr int kFewSmall = 10, kFewLarge = 7, kFewHuge = 3;   // clusters below, 
 constexpr double kRoundingCost = 1e5;
 constexpr int kFirst = 512;              // cells of the first round
 constexpr int kMaxPer = 1024;            // cells per layer of a window later
-constexpr int kMaxMerged = 8;            // a layer's range: up to this many times as many
+constexpr int kMerged = 8, kMaxMerged = 32;   // a layer's range: this many times as many
 constexpr int kMaxClusters = 512;
 constexpr int kMaxSplit = 8;             // cells of one that is kept, beside a window's share
 constexpr int kMaxRounds = 5;
-constexpr int kMaxPoints = 1 << 17;      // of a grid; the rules below keep to 88,200
+constexpr int kMaxPoints = 1 << 17;      // of a grid
 
 // What a round leaves for the host.
 struct RoundCtl {
@@ -624,22 +624,30 @@ __global__ __launch_bounds__(kThreads) void prune_kernel(View V)
     }
 }
 
-// Inclusive scan over the workgroup of one whole number per thread.
+// Exclusive scan over the workgroup of one whole number per thread, and the
+// total: within the waves by lane moves, their totals (in a) by every thread.
 template <int NT>
-__device__ __forceinline__ int32_t block_scan_incl(int32_t x, int32_t *a)
+__device__ __forceinline__ int32_t block_scan_excl(int32_t x, int32_t *a, int32_t &total)
 {
-    const int t = threadIdx.x;
-    __syncthreads();
-    a[t] = x;
-    __syncthreads();
-    for (int off = 1; off < NT; off <<= 1) {
-        const int32_t o = t >= off ? a[t - off] : 0;
-        __syncthreads();
-        x += o;
-        a[t] = x;
-        __syncthreads();
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    int32_t y = x;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t z = __shfl_up(y, o, kWave);
+        y += lane >= o ? z : 0;
     }
-    return x;
+    __syncthreads();                             // the totals of the scan before are read
+    if (lane == kWave - 1)
+        a[wave] = y;
+    __syncthreads();
+    int32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w) {
+        before += w < wave ? a[w] : 0;
+        total += a[w];
+    }
+    return before + y - x;
 }
 
 // The next round's windows: the runs of neighbouring cells that some layer
@@ -657,7 +665,7 @@ static_assert(kMaxClusters <= kWinThreads, "a thread per layer");
 
 __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
 {
-    __shared__ int32_t a[kWinThreads];
+    __shared__ int32_t a[kWinThreads / kWave];
     __shared__ int32_t lo[kMaxClusters], hi[kMaxClusters];
     __shared__ uint64_t cm[kMaxPoints / 64], pm[kMaxPoints / 64];
     __shared__ int32_t split, extra, rows, fail, all, exact;
@@ -718,12 +726,10 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
         m += __popcll(first & cm[w]);
         k += __popcll(cm[w]);
     }
-    int32_t ws = block_scan_incl<kWinThreads>(s, a) - s;
-    const int32_t nseg = a[kWinThreads - 1];
-    int32_t wm = block_scan_incl<kWinThreads>(m, a) - m;
-    const int32_t wide = a[kWinThreads - 1];
-    int32_t wk = block_scan_incl<kWinThreads>(k, a) - k;
-    const int32_t cells = a[kWinThreads - 1];
+    int32_t nseg, wide, cells;
+    int32_t ws = block_scan_excl<kWinThreads>(s, a, nseg);
+    int32_t wm = block_scan_excl<kWinThreads>(m, a, wide);
+    int32_t wk = block_scan_excl<kWinThreads>(k, a, cells);
     // the windows' first and last grid points
     for (int32_t w = w0; w < w1; ++w) {
         const uint64_t C = cm[w], first = starts(w), last = (C | pm[w] | before(w)) & ~C;
@@ -752,8 +758,8 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
         V.segQ[z] = q;
         l += q - p + 1;
     }
-    int32_t wl = block_scan_incl<kWinThreads>(l, a) - l;
-    const int32_t span = a[kWinThreads - 1];
+    int32_t span;
+    int32_t wl = block_scan_excl<kWinThreads>(l, a, span);
     for (int32_t z = z0; z < z1; ++z) {
         V.lpre[z] = wl;
         wl += V.segQ[z] - V.segP[z] + 1;
@@ -815,8 +821,8 @@ __global__ __launch_bounds__(kWinThreads) void windows_kernel(View V)
             atomicAnd(&exact, 0);
         b += x;
     }
-    int32_t o = block_scan_incl<kWinThreads>(b, a) - b;
-    const int32_t total = a[kWinThreads - 1];
+    int32_t total;
+    int32_t o = block_scan_excl<kWinThreads>(b, a, total);
     for (int32_t z = z0; z < z1; ++z) {
         V.base[z] = o;
         o += points(z);
@@ -937,7 +943,7 @@ size_t place(char *ws, int64_t n, int32_t ke, int32_t per, int32_t merged, View 
 
 bool kmeans_windows_apply(int64_t n, int64_t k)
 {
-    return n >= kFromN && k >= (n < kLargeN ? kFewSmall : n < kHugeN ? kFewLarge : kFewHuge);
+    return n >= kFromN && k >= (n < kHugeN ? kFew : kFewHuge);
 }
 
 hipError_t launch_gap_stats(const double *sv, const double2 *SS, int64_t n, GapStats *gs,
@@ -1027,14 +1033,23 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
     if (!(gs.s2 > 0x1p-900 && gs.s2 < 0x1p900) || !worth_it(gs, n, ke))
         return hipSuccess;
     // cells of the first round, and rows of a layer: as many as are useful and
-    // the scratch holds; with few per cluster the windows do not shrink (one is
-    // about sqrt(4 ke) / (cells per cluster) of it).  10 ke^1.5: n = 20,000, k =
-    // 24 (10.3) 1.38 times as fast, 12,000 and 24 (7.0) 1.29 with a tenth of the
-    // draws at 0.7, 40,000 and 48 (5.4) 1.15 with a third; 1,050,000 and 70
-    // (14) 3.8, 600,000 and 100 (8.2) 2.9 with one in thirteen at 0.75, 1,050,000 and
-    // 120 (6.2) 2.1 with two in five at 0.8
+    // the scratch holds.  With few per cluster the windows do not shrink (one is
+    // about sqrt(4 ke) / (cells per cluster) of it): 10 ke^1.5 cells, of up to 32
+    // x kMaxPer, and from 2^17 values fewer are not tried (n = 600,000, k = 100, 130
+    // with 8 x: 2.9, 2.2 times as fast and two and eight draws of 26 at 0.7 to 0.85,
+    // with 16 x: 2.8, 2.7 and none; k = 70: 3.2 and 2.9; n = 2M, k = 150 with 16, 32 x:
+    // 2.1, 2.8; k = 200 with 32 x, 7 ke^1.5: 1.8, five draws of 13 at 0.7 to 0.86).
+    // With fewer values a range is every position soon, and 5.5 ke^1.5 will do:
+    // embeddings with n = 8,192, k = 24 (5.7): 1.48; of the shapes at n = 12,000, k =
+    // 24 (7.0) and 20,000, 32 (5.9) a tenth take 0.7 times as long again for 1.29
+    // and 1.24 on average; 40,000, 48 (5.4): a third, for 1.15.
     View V{};
-    int32_t per = (int32_t)(n / 4 < kMaxPer ? n / 4 : kMaxPer), merged = kMaxMerged;
+    const double least = (n < kLargeN ? 5.5 : 10.0) * ke * sqrt((double)ke);
+    int32_t per = (int32_t)(n / 4 < kMaxPer ? n / 4 : kMaxPer), merged = kMerged;
+    if (per > kMaxPoints / (ke - 1) - 1)
+        per = kMaxPoints / (ke - 1) - 1;
+    while (merged < kMaxMerged && (double)per * merged < least)
+        merged *= 2;
     while (per >= 32 && place(nullptr, n, ke, per, merged, &V) > ws_bytes) {
         if (merged > 2)
             merged /= 2;
@@ -1042,11 +1057,9 @@ hipError_t kmeans_windows(const double *sv, const int32_t *run, const double2 *S
             per -= (per + 15) / 16;
     }
     const double cells = (double)per * (merged < ke - 1 ? merged : ke - 1);
-    if (per < 32 || per < 2 * ke || (cells < (double)n && cells < 10.0 * ke * sqrt((double)ke)))
+    if (per < 32 || per < 2 * ke || (cells < (double)n && cells < least))
         return hipSuccess;
     place(static_cast<char *>(ws), n, ke, per, merged, &V);
-    if (V.points > kMaxPoints)
-        return hipSuccess;                           // not reached
     V.sv = sv;
     V.run = run;
     V.SS = SS;

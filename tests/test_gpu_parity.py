@@ -475,15 +475,15 @@ def _clusters(n, m, width, rng):
 
 
 @pytest.mark.parametrize("n,k,shape,solver", [
-    (8191, 10, "normal", "rows"), (8192, 9, "normal", "rows"), (8192, 10, "normal", "windows"),
-    (8192, 24, "normal", "rows"), (20011, 10, "normal", "windows"),
+    (8191, 10, "normal", "rows"), (8192, 6, "normal", "rows"), (8192, 7, "normal", "windows"),
+    (8192, 24, "normal", "windows"), (8192, 40, "normal", "rows"),
     (20011, 16, "tail", "windows"), (60000, 24, "tight", "windows"),
-    (60000, 24, "fewer", "rows"), (131071, 9, "normal", "rows"),
-    (131072, 7, "normal", "windows"), (131072, 24, "fewer", "windows"),
-    (262143, 6, "tail", "rows"), (262144, 3, "tail", "windows"),
-    (262144, 50, "fewer", "windows"), (300007, 12, "rounding", "rows"),
-    (300007, 40, "tight", "windows"), (400000, 60, "fewer", "windows"),
-    (300007, 512, "normal", "rows"), (600001, 80, "uniform", "windows")])
+    (60000, 24, "fewer", "rows"), (131071, 12, "fewer", "rows"),
+    (131072, 12, "fewer", "windows"), (262143, 6, "tail", "rows"),
+    (262144, 3, "tail", "windows"), (262144, 50, "fewer", "windows"),
+    (300007, 12, "rounding", "rows"), (300007, 40, "tight", "windows"),
+    (400000, 60, "fewer", "windows"), (300007, 512, "normal", "rows"),
+    (600001, 110, "uniform", "windows")])
 def test_kmeans1d_solver(g, orc, monkeypatch, n, k, shape, solver):
     """Which values the windows solve and which take the full programme, on
     both sides of the rules (sizes, clusters, scratch for the cells, fewer
