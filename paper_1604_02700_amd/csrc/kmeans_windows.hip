@@ -60,8 +60,8 @@ constexpr int kWaves = kThreads / kWave;
 // 20,000, 1.0 at 60,000, with clusters of widely different widths down to 0.8;
 // k = 10: 1.25, 1.23, 1.15; k = 6: 1.07, 1.07.
 //   From 2^18 values: n = 270,000, k = 3, 7, 24: 1.05, 1.54, 2.4; n = 600,000, k =
-// 5, 40: 1.5, 3.1; n = 2M, k = 3, 5, 50: 1.29, 1.76, 4.5 (19.2 ms without); a few in
-// a hundred, whose cost is near the rounding, down to 0.77.
+// 5, 40: 1.5, 3.1; n = 2M, k = 3, 5, 50: 1.29, 1.76, 4.5 (19.2 ms without); one or
+// two in a hundred, most of a cost near the rounding, down to 0.73.
 // Cells: a first round of 1,024 costs 0.1-0.3 ms more, of 256 leaves wider
 // windows; rows of 4 x kMaxPer instead of 8 x lose from k = 50 on.  Splits by 4,
 // 8, 16 and as many as fit: the clustering's embeddings at n = 2M, k = 50: 3.23,
@@ -654,12 +654,13 @@ __device__ __forceinline__ int32_t block_scan_excl(int32_t x, int32_t *a, int32_
 // keeps (a kept point beside no kept cell is one by itself), each cut into
 // `split` cells for every one it had and `extra` more, as many as the grid
 // and the rows hold, half of the room for either, or into every position
-// where there is room for all of them.  A layer's range is
-// that of the cells it keeps, made monotone over the layers; what lies in it
-// between windows is left out, so that a few far apart ways to place the
-// cuts (k above the number of clusters) do not keep all that lies between.
-// One workgroup, bound by the latency of its few dependent passes: 16 us for
-// 513 points, 52 for 49,000 (119 with a thread's run of marks read at a time).
+// where there is room for all of them.  A layer's range is that of the cells
+// it keeps, made monotone over the layers; what lies in it between windows is
+// left out, so that a few far apart ways to place the cuts (k above the number
+// of clusters) do not keep all that lies between.
+// One workgroup, bound by the latency of its few dependent passes: 15 us for
+// 513 points, 40 for 49,000 (119 with a thread's run of marks read at a time
+// and scans behind twenty barriers).
 constexpr int kWinThreads = 1024;
 static_assert(kMaxClusters <= kWinThreads, "a thread per layer");
 
